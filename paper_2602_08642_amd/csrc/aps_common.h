@@ -142,4 +142,10 @@ int sampler_cnn(const void* x, int N, int H, int W, int C, int Cin, const void* 
                 const void* w1, const float* b1, const void* w2, const float* b2, int dtype, float* z,
                 hipStream_t st);
 
+// bf16 weight and bias gradients (wgrad.hip); arguments as aps_conv2d_bwd_weight, checked there.
+size_t wgrad_sweep_workspace(int N, int H, int W, int Cin, int Cout, int KS);
+void wgrad_sweep(const void* x, const void* x2, int mode, int N, int H, int W, int Cx, int C2,
+                 const void* dy, const void* ymask, int ldy, int Cout, int KS, float* dw, float* db,
+                 void* ws, hipStream_t st);
+
 }  // namespace aps

@@ -1764,7 +1764,7 @@ __global__ __launch_bounds__(256) void k_input_grad(int mode, const T* __restric
 }
 
 // ---- weight gradient: dW[co][tap][ci] = sum_px dY[px][co] * X[px + d_tap][ci] -------------
-// M = cout (16 per MFMA tile), N = cin (16), K = pixels: 2-row x 64-column pixel blocks, the
+// fp32 only (bf16: wgrad.hip).  M = cout (16 per MFMA tile), N = cin (16), K = pixels: 2-row x 64-column pixel blocks, the
 // block's dY (cout-major) and its input tile with halo (cin-major) staged in LDS.  Pixel blocks
 // are split across workgroups; each split writes its partial dW and a second pass sums the
 // splits in a fixed order (deterministic).
@@ -1787,12 +1787,6 @@ __device__ inline void frag_load_lds<float>(Frag<float>& f, const float* p) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) f.v[e] = p[e];
 }
-template <>
-__device__ inline void frag_load_lds<uint16_t>(Frag<uint16_t>& f, const uint16_t* p) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f.v[e] = p[e];
-}
-
 template <typename T, int KS>
 __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
   constexpr int R = KS / 2;
@@ -2173,7 +2167,8 @@ size_t aps_conv2d_bwd_weight_workspace_size(int N, int H, int W, int Cx, int C2,
                                             int ksize) {
   if (N <= 0 || H <= 0 || W <= 0 || Cout <= 0 || Cx <= 0) return 256;
   const WgradPlan p = wgrad_plan(N, H, W, Cx + C2, Cout, ksize);
-  return ((p.part_bytes + 255) / 256) * 256 + p.bias_blocks * Cout * sizeof(float) + 256;
+  const size_t f32 = ((p.part_bytes + 255) / 256) * 256 + p.bias_blocks * Cout * sizeof(float);
+  return std::max(f32, wgrad_sweep_workspace(N, H, W, Cx + C2, Cout, ksize)) + 256;
 }
 
 int aps_conv2d_bwd_weight(const void* x, const void* x2, int mode, int N, int H, int W, int Cx,
@@ -2195,6 +2190,12 @@ int aps_conv2d_bwd_weight(const void* x, const void* x2, int mode, int N, int H,
   if (!x || !dy || !dw) return APS_ERR_NULL;
   if (!ws || ws_bytes < aps_conv2d_bwd_weight_workspace_size(N, H, W, Cx, C2, Cout, ksize))
     return APS_ERR_WORKSPACE;
+  if (dtype == APS_BF16) {
+    wgrad_sweep(x, x2, mode, N, H, W, Cx, C2, dy, ymask, ldy, Cout, ksize, dw, db, ws, as_stream(stream));
+    APS_LAUNCH_CHECK();
+    return APS_OK;
+  }
+  if (dtype != APS_F32) return APS_ERR_UNSUPPORTED;
   const int Cin = Cx + C2;
   const WgradPlan p = wgrad_plan(N, H, W, Cin, Cout, ksize);
   WgradArgs a{};
@@ -2221,29 +2222,17 @@ int aps_conv2d_bwd_weight(const void* x, const void* x2, int mode, int N, int H,
   float* bpart = reinterpret_cast<float*>(static_cast<char*>(ws) + ((p.part_bytes + 255) / 256) * 256);
   hipStream_t st = as_stream(stream);
   dim3 grid(p.splits, p.CoutP / 32, p.nchunk);
-  if (dtype == APS_F32) {
-    if (ksize == 3) k_wgrad<float, 3><<<grid, 256, 0, st>>>(a);
-    else k_wgrad<float, 1><<<grid, 256, 0, st>>>(a);
-  } else if (dtype == APS_BF16) {
-    if (ksize == 3) k_wgrad<uint16_t, 3><<<grid, 256, 0, st>>>(a);
-    else k_wgrad<uint16_t, 1><<<grid, 256, 0, st>>>(a);
-  } else {
-    return APS_ERR_UNSUPPORTED;
-  }
+  if (ksize == 3) k_wgrad<float, 3><<<grid, 256, 0, st>>>(a);
+  else k_wgrad<float, 1><<<grid, 256, 0, st>>>(a);
   const size_t nw = (size_t)Cout * ksize * ksize * Cin;
   k_wgrad_reduce<<<(unsigned)((nw + 31) / 32), 256, 0, st>>>(a.part, p.splits, Cout,
                                                                 ksize * ksize, Cin, p.CoutP, p.CinP,
                                                                 dw);
   if (db) {
     const size_t npix = (size_t)N * H * W;
-    if (dtype == APS_F32)
-      k_bias_partial<float><<<(unsigned)p.bias_blocks, 256, 0, st>>>(
-          static_cast<const float*>(dy), static_cast<const float*>(ymask), ldy, Cout, npix,
-          p.bias_per, bpart);
-    else
-      k_bias_partial<uint16_t><<<(unsigned)p.bias_blocks, 256, 0, st>>>(
-          static_cast<const uint16_t*>(dy), static_cast<const uint16_t*>(ymask), ldy, Cout, npix,
-          p.bias_per, bpart);
+    k_bias_partial<float><<<(unsigned)p.bias_blocks, 256, 0, st>>>(
+        static_cast<const float*>(dy), static_cast<const float*>(ymask), ldy, Cout, npix, p.bias_per,
+        bpart);
     k_bias_reduce<<<Cout, 256, 0, st>>>(bpart, (int)p.bias_blocks, Cout, db);
   }
   APS_LAUNCH_CHECK();
