@@ -3,335 +3,19 @@
 //   K = taps x input channels, walked in chunks of 32 channels.
 // The input tile of a chunk, with its 1-pixel halo, is staged once in LDS and read by all
 // taps; weights are pre-packed in MFMA fragment order and read straight into registers.
-// bf16: v_mfma_f32_16x16x32_bf16 (fp32 accumulate).  f32: v_mfma_f32_16x16x4f32.
+// bf16: v_mfma_f32_16x16x32_bf16 (fp32 accumulate).  f32: v_mfma_f32_16x16x4f32 for the layers
+// here; fp32 3x3 layers in 32-channel chunks run on fp16 halves (conv_f32.hip).
 // Input transforms fused into the staging: 2x2 average pool of a finer tensor, or nearest
 // 2x upsampling of a coarser tensor concatenated with a skip tensor (U-Net decoder).
 // Epilogue: bias, optional ReLU, store (f32 or bf16).
 #include <algorithm>
 #include <type_traits>
 
-#include "aps_common.h"
-#include "mfma_frag.h"
+#include "conv_common.h"
 
 using namespace aps;
 
 namespace {
-
-constexpr int kChunk = 32;
-constexpr int kMaxTM = 4;
-constexpr int kModeReluMask = 3;  // internal staging mode of the data-gradient convolution
-
-struct ConvArgs {
-  const void* x;
-  const void* x2;
-  int N, H, W;   // output (= conv input after the transform) size
-  int Cx, C2, mode;
-  const void* wp;
-  const float* bias;
-  int Cout, nchunk, ntx;
-  void* y;
-  int ldy, relu;
-  // optional 1x1 head fused into the epilogue (see k_conv); store_main = also write y
-  const void* hw;
-  const float* hb;
-  int hK;
-  void* hy;
-  int hldy, store_main;
-  // optional side output of three head channels [hside_off, hside_off + 3) as [N,H,W,4] (the
-  // fourth entry 0), written from the staged logit rows (conv_epilogue)
-  void* hside;
-  int hside_off;
-  // optional 2x2 average pool of the (bf16-rounded) output, [N, H/2, W/2, Cout] (k_conv_lds)
-  void* pool;
-  int ntiles, nco;  // pixel tiles per image, output-channel blocks (block order: xcd_tile)
-};
-
-// Blocks are dispatched round-robin over the 8 XCDs (block id % 8), each with its own L2.  XCD x
-// takes the contiguous tile range [x T8, (x+1) T8) and, per tile, all channel blocks back to back,
-// so the halo rows shared by neighbouring tiles and the input tile shared by a tile's channel
-// blocks are re-read from that XCD's L2 rather than from HBM.  grid.x = 8 T8 nco; blocks past the
-// last tile exit.
-struct TileId {
-  int tile, cob;
-};
-__device__ inline TileId xcd_tile(int id, int ntiles, int nco) {
-  const int t8 = (ntiles + 7) / 8, xcd = id & 7, k = id >> 3;
-  return TileId{xcd * t8 + k / nco, k % nco};
-}
-inline int xcd_grid(int ntiles, int nco) { return 8 * ((ntiles + 7) / 8) * nco; }
-
-// ---- 8-element vectors of the storage type ---------------------------------------------
-struct V8f {
-  float v[8];
-};
-
-__device__ inline V8f load8(const float* p) {
-  const float4 a = *reinterpret_cast<const float4*>(p);
-  const float4 b = *reinterpret_cast<const float4*>(p + 4);
-  return V8f{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
-}
-__device__ inline V8f load8(const uint16_t* p) {
-  const u16x8 h = *reinterpret_cast<const u16x8*>(p);
-  V8f r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r.v[e] = bf2f(h[e]);
-  return r;
-}
-__device__ inline void store8(float* p, const V8f& r) {
-  *reinterpret_cast<float4*>(p) = make_float4(r.v[0], r.v[1], r.v[2], r.v[3]);
-  *reinterpret_cast<float4*>(p + 4) = make_float4(r.v[4], r.v[5], r.v[6], r.v[7]);
-}
-__device__ inline void store8(uint16_t* p, const V8f& r) {
-  u16x8 h;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = f2bf(r.v[e]);
-  *reinterpret_cast<u16x8*>(p) = h;
-}
-// Stage channels [ci, ci+8) of input pixel (iy, ix) into LDS.
-template <typename T>
-__device__ inline void stage8(const ConvArgs& a, int n, int iy, int ix, int ci, T* dst) {
-  const int Cin = a.Cx + a.C2;
-  if (iy < 0 || iy >= a.H || ix < 0 || ix >= a.W || ci >= Cin) {
-    zero8(dst);
-    return;
-  }
-  const T* x = static_cast<const T*>(a.x);
-  if ((a.mode == APS_CONV_DIRECT || a.mode == kModeReluMask) && ci + 8 > a.Cx) {
-    // channel tail of a row whose stride is not a multiple of 8 (padded logit gradients)
-    const size_t o = (((size_t)n * a.H + iy) * a.W + ix) * a.Cx + ci;
-    const T* y = static_cast<const T*>(a.x2);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool ok = ci + e < a.Cx && (a.mode == APS_CONV_DIRECT || Ld<T>::get(y, o + e) > 0.f);
-      dst[e] = ok ? x[o + e] : T(0);
-    }
-  } else if (a.mode == APS_CONV_DIRECT) {
-    copy8(dst, x + (((size_t)n * a.H + iy) * a.W + ix) * a.Cx + ci);
-  } else if (a.mode == kModeReluMask) {
-    // x = dLoss/dy, x2 = y (post-ReLU output, same layout): stage dy where y > 0, else 0
-    const size_t o = (((size_t)n * a.H + iy) * a.W + ix) * a.Cx + ci;
-    const V8f g = load8(x + o), y = load8(static_cast<const T*>(a.x2) + o);
-    V8f r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r.v[e] = y.v[e] > 0.f ? g.v[e] : 0.f;
-    store8(dst, r);
-  } else if (a.mode == APS_CONV_POOL2) {
-    const int W2 = 2 * a.W;
-    const T* p = x + (((size_t)n * 2 * a.H + 2 * iy) * W2 + 2 * ix) * a.Cx + ci;
-    const V8f q0 = load8(p), q1 = load8(p + a.Cx), q2 = load8(p + (size_t)W2 * a.Cx),
-              q3 = load8(p + (size_t)W2 * a.Cx + a.Cx);
-    V8f r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r.v[e] = ((q0.v[e] + q1.v[e]) + (q2.v[e] + q3.v[e])) * 0.25f;
-    store8(dst, r);
-  } else {  // APS_CONV_UP2_CAT
-    if (ci < a.Cx) {
-      const int Hh = a.H / 2, Wh = a.W / 2;
-      copy8(dst, x + (((size_t)n * Hh + iy / 2) * Wh + ix / 2) * a.Cx + ci);
-    } else {
-      const T* x2 = static_cast<const T*>(a.x2);
-      copy8(dst, x2 + (((size_t)n * a.H + iy) * a.W + ix) * a.C2 + (ci - a.Cx));
-    }
-  }
-}
-
-template <typename TO>
-__device__ inline void store_out(TO* p, int ldy, int co0, int Cout, const float* v);
-template <>
-__device__ inline void store_out<float>(float* p, int ldy, int co0, int Cout, const float* v) {
-  if ((ldy & 3) == 0 && co0 + 4 <= ldy) {
-    *reinterpret_cast<float4*>(p + co0) = make_float4(v[0], v[1], v[2], v[3]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (co0 + q < Cout) p[co0 + q] = v[q];
-  }
-}
-template <>
-__device__ inline void store_out<uint16_t>(uint16_t* p, int ldy, int co0, int Cout, const float* v) {
-  if ((ldy & 3) == 0 && co0 + 4 <= ldy) {
-    *reinterpret_cast<u16x4*>(p + co0) = f2bf4(v[0], v[1], v[2], v[3]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (co0 + q < Cout) p[co0 + q] = f2bf(v[q]);
-  }
-}
-
-// Epilogue shared by the convolution kernels: bias, optional ReLU, store; with HEAD, the fused
-// 1x1 head.  acc[m][j] holds output rows row0 + j, channels 16 (cob TM + m) + 4 (lane / 16) + q,
-// pixel column tx0 + lane % 16.  Xs is the block's LDS tile, reused by the head's re-layout.
-// s_waitcnt immediate (gfx9 encoding) that waits for all vector memory operations only:
-// vmcnt = 0, expcnt = 7 and lgkmcnt = 15 (no wait on those).
-constexpr int kWaitVm0 = 0x0F70;
-
-// LDS the fused head's epilogue needs, in elements of the tile type T: per wave a [16 px][16 TM
-// ch] re-layout region (row pitch 16 TM + 8 or + 4), then per wave a [16 px][<= 16 HM ch] staging
-// region for the head outputs (type TO).  The kernels size their input tile at least this large.
-// HM = head m-tiles (4: up to 64 logits, 5: up to 80); 0 = no fused head.
-template <typename T, typename TO, int TM, int HM>
-constexpr int head_lds_elems() {
-  return 4 * 16 * (TM * 16 + (sizeof(T) == 2 ? 8 : 4)) + 4 * 16 * 16 * HM * (int)(sizeof(TO) / sizeof(T));
-}
-
-template <typename T, typename TO, int TM, int TN, int HEAD, bool BIAS_IN_ACC = false>
-__device__ inline void conv_epilogue(const ConvArgs& a, f32x4 (&acc)[TM][TN], int row0, int tx0,
-                                     int cob, int n, int lane, int wave, T* Xs) {
-  TO* y = static_cast<TO*>(a.y);
-  const int col = tx0 + (lane & 15);
-  float bv[TM][4];  // this lane's bias values, loaded once
-#pragma unroll
-  for (int m = 0; m < TM; ++m) {
-    const int co0 = (cob * TM + m) * 16 + 4 * (lane >> 4);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      bv[m][q] = !BIAS_IN_ACC && co0 + q < a.Cout && a.bias ? a.bias[co0 + q] : 0.f;
-  }
-  if constexpr (!HEAD) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int row = row0 + j;
-      if (row >= a.H || col >= a.W) continue;
-      TO* py = y + (((size_t)n * a.H + row) * a.W + col) * a.ldy;
-#pragma unroll
-      for (int m = 0; m < TM; ++m) {
-        const int co0 = (cob * TM + m) * 16 + 4 * (lane >> 4);
-        if (co0 >= a.Cout) continue;
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float t = acc[m][j][q] + bv[m][q];
-          v[q] = a.relu ? fmaxf(t, 0.f) : t;
-        }
-        store_out<TO>(py, a.ldy, co0, a.Cout, v);
-      }
-    }
-  } else {
-    // Fused 1x1 head on this layer's output (all Cout = 16 TM channels are in this block):
-    // each wave re-lays its row-j tile [16 px][16 TM ch] out through its own LDS region as MFMA
-    // B fragments and multiplies it by the packed head weights (held in registers), the same
-    // operands in the same order as the stand-alone 1x1 convolution of the stored tile.  The
-    // regions are per wave, so after the caller's barrier only wave-local ordering is needed.
-    // Head outputs go out through a second per-wave region: the row's [npx][hldy] run of
-    // logits is contiguous in memory, so the wave writes it with 16-byte vector stores to
-    // consecutive addresses (channels in [hK, hldy) as zeros) instead of one 8- or 16-byte piece
-    // per lane and 16-channel group at the pixel stride, which measured about twice as slow.
-    constexpr int CC = TM * 16, YP = CC + (sizeof(T) == 2 ? 8 : 4), HM = HEAD;
-    T* Ys = Xs + wave * 16 * YP;
-    TO* Os = reinterpret_cast<TO*>(Xs + 4 * 16 * YP) + wave * 16 * 16 * HM;
-    const bool staged = a.hldy <= 16 * HM && (a.hldy * (int)sizeof(TO)) % 16 == 0 &&
-                        (reinterpret_cast<uintptr_t>(a.hy) & 15) == 0;
-    const int npx = a.W - tx0 < 16 ? a.W - tx0 : 16;
-    const T* hw = static_cast<const T*>(a.hw);
-    TO* hy = static_cast<TO*>(a.hy);
-    Frag<T> hwf[HM][TM / 2];
-#pragma unroll
-    for (int mh = 0; mh < HM; ++mh)
-#pragma unroll
-      for (int cc = 0; cc < TM / 2; ++cc)
-        if (mh * 16 < a.hK) frag_load(hwf[mh][cc], hw + ((((size_t)mh * (TM / 2)) + cc) * 64 + lane) * 8);
-    // head biases: unconditional loads (index clamped to a valid entry), then one wait for them
-    // and the head weights here.  Left to the compiler, the wait for a value loaded under a
-    // branch is placed at each use inside the later (branching) store code, and as vmcnt also
-    // counts stores, every one of those waits would drain all stores issued before it.
-    float hb[HM][4];
-#pragma unroll
-    for (int mh = 0; mh < HM; ++mh)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = mh * 16 + 4 * (lane >> 4) + q;
-        const float v = a.hb[k < a.hK ? k : 0];
-        hb[mh][q] = k < a.hK ? v : 0.f;
-      }
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int row = row0 + j;
-      const bool inpx = row < a.H && col < a.W;
-#pragma unroll
-      for (int m = 0; m < TM; ++m) {
-        const int co0 = m * 16 + 4 * (lane >> 4);
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float t = acc[m][j][q] + bv[m][q];
-          v[q] = a.relu ? fmaxf(t, 0.f) : t;
-        }
-        if constexpr (sizeof(T) == 2)
-          *reinterpret_cast<u16x4*>(Ys + (lane & 15) * YP + co0) = f2bf4(v[0], v[1], v[2], v[3]);
-        else
-          *reinterpret_cast<float4*>(Ys + (lane & 15) * YP + co0) = make_float4(v[0], v[1], v[2], v[3]);
-        if (a.store_main && inpx)
-          store_out<TO>(y + (((size_t)n * a.H + row) * a.W + col) * a.ldy, a.ldy, co0, a.Cout, v);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      Frag<T> bf[TM / 2];
-#pragma unroll
-      for (int cc = 0; cc < TM / 2; ++cc) frag_load(bf[cc], Ys + (lane & 15) * YP + 32 * cc + 8 * (lane >> 4));
-      if (staged) {
-#pragma unroll
-        for (int mh = 0; mh < HM; ++mh) {
-          const int k0 = mh * 16 + 4 * (lane >> 4);
-          if (mh * 16 >= a.hldy) break;
-          f32x4 h = f32x4{0.f, 0.f, 0.f, 0.f};
-          if (mh * 16 < a.hK) {
-#pragma unroll
-            for (int cc = 0; cc < TM / 2; ++cc) h = mma(hwf[mh][cc], bf[cc], h);
-          }
-          float o[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) o[q] = k0 + q < a.hK ? h[q] + hb[mh][q] : 0.f;
-          if (k0 < a.hldy) {
-            if constexpr (sizeof(TO) == 2)
-              *reinterpret_cast<u16x4*>(Os + (lane & 15) * a.hldy + k0) = f2bf4(o[0], o[1], o[2], o[3]);
-            else
-              *reinterpret_cast<f32x4*>(Os + (lane & 15) * a.hldy + k0) = f32x4{o[0], o[1], o[2], o[3]};
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (row < a.H) {
-          const int nvec = npx * a.hldy * (int)sizeof(TO) / 16;
-          uint4* dst = reinterpret_cast<uint4*>(hy + (((size_t)n * a.H + row) * a.W + tx0) * a.hldy);
-          const uint4* src = reinterpret_cast<const uint4*>(Os);
-          // nontemporal: the logits are read back only by the filter, after the other heads
-          for (int v = lane; v < nvec; v += 64)
-            __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(src)[v], reinterpret_cast<u32x4*>(dst) + v);
-          if (a.hside && lane < npx) {
-            const TO* op = Os + lane * a.hldy + a.hside_off;
-            TO* sp = static_cast<TO*>(a.hside) + (((size_t)n * a.H + row) * a.W + tx0 + lane) * 4;
-            if constexpr (sizeof(TO) == 2)
-              *reinterpret_cast<u16x4*>(sp) = u16x4{op[0], op[1], op[2], (uint16_t)0};
-            else
-              *reinterpret_cast<f32x4*>(sp) = f32x4{op[0], op[1], op[2], 0.f};
-          }
-        }
-      } else {
-#pragma unroll
-        for (int mh = 0; mh < HM; ++mh) {
-          if (mh * 16 >= a.hK) break;
-          f32x4 h = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int cc = 0; cc < TM / 2; ++cc) h = mma(hwf[mh][cc], bf[cc], h);
-          const int k0 = mh * 16 + 4 * (lane >> 4);
-          if (inpx && k0 < a.hK) {
-            float o[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] = h[q] + hb[mh][q];
-            store_out<TO>(hy + (((size_t)n * a.H + row) * a.W + col) * a.hldy, a.hldy, k0, a.hK, o);
-          }
-        }
-      }
-      // the next row's re-layout overwrites Ys
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  }
-}
 
 // CG = 8-channel input groups per pixel in the K layout.  CG = 4: K walks 32-channel chunks,
 // one tap per MFMA step.  CG = 1 or 2 (inputs of at most 8 or 16 channels, a single chunk): K
@@ -649,270 +333,6 @@ __global__ __launch_bounds__(256, 2) void k_conv_lds(ConvArgs a) {
   }
 }
 
-// ---- fp32 3x3 convolution with both MFMA operands in LDS --------------------------------------
-// k_conv_lds for fp32 on v_mfma_f32_16x16x4_f32: chunks of 16 input channels (4 per lane per
-// fragment, 4 MFMAs per fragment pair), pixel stride 20 floats in LDS (80 B, conflict-free for the
-// 16 lanes of a B fragment), weights packed by k_pack_f32c16.  Same tiling, row reuse, prefetch
-// and epilogue rules as the bf16 kernel; the pooled copy averages the fp32 outputs in the order of
-// the POOL2 input transform.
-__device__ inline f32x4 mma4(f32x4 a, f32x4 b, f32x4 c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
-}
-
-// The value of lane l ^ 1 (DPP quad_perm [1,0,3,2]).  By value on purpose: a bit cast applied
-// directly to a vector-element subscript was compiled as a read of element 0.
-__device__ inline float lane_xor1(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
-}
-
-template <int TM, int TN>
-__device__ inline void lds_epilogue_f32(const ConvArgs& a, f32x4 (&acc)[TM][TN], int row0, int tx0,
-                                        int cob, int n, int lane) {
-  float* y = static_cast<float*>(a.y);
-  float* yp = static_cast<float*>(a.pool);
-  const int col = tx0 + (lane & 15);
-#pragma unroll
-  for (int j0 = 0; j0 < TN; j0 += 2) {
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-      const int co = (cob * TM + m) * 16 + 4 * (lane >> 4);
-      if (co >= a.Cout) continue;
-      f32x4 h[2];
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = j0 + jj, row = row0 + j;
-        f32x4 v = acc[m][j];
-        if (a.relu) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q], 0.f);
-        }
-        h[jj] = v;
-        if (row < a.H && col < a.W) {
-          const float vv[4] = {v[0], v[1], v[2], v[3]};
-          store_out<float>(y + (((size_t)n * a.H + row) * a.W + col) * a.ldy, a.ldy, co, a.Cout, vv);
-        }
-      }
-      if (yp) {
-        f32x4 nb[2];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) nb[jj][q] = lane_xor1(h[jj][q]);
-        const int row = row0 + j0;
-        if ((lane & 1) == 0 && row < a.H && col < a.W)
-          *reinterpret_cast<f32x4*>(yp + (((size_t)n * (a.H / 2) + row / 2) * (a.W / 2) + col / 2) * a.Cout + co) =
-              ((h[0] + nb[0]) + (h[1] + nb[1])) * 0.25f;
-      }
-    }
-  }
-}
-
-template <int MODE, int TM, int TN, int HEAD>
-__global__ __launch_bounds__(256, 2) void k_conv_lds_f32(ConvArgs a) {
-  constexpr int KC = 16, ROWS = 4 * TN, SH = ROWS + 2, SW = 18, PS = 20;
-  constexpr int NXV = SH * SW * 4, NXT = (NXV + 255) / 256;  // input 16-B vectors per chunk
-  constexpr int NAV = TM * 9 * 64, NAT = (NAV + 255) / 256;  // weight 16-B vectors per chunk
-  // the fused head's epilogue reuses Xs (re-layout and output staging regions)
-  constexpr int XS_TILE = SH * SW * PS, XS_HEAD = HEAD ? head_lds_elems<float, float, TM, HEAD>() : 0;
-  __shared__ __attribute__((aligned(16))) float Xs[XS_TILE > XS_HEAD ? XS_TILE : XS_HEAD];
-  __shared__ __attribute__((aligned(16))) float As[NAV * 4];
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const TileId tid_ = xcd_tile(blockIdx.x, a.ntiles, a.nco);
-  if (tid_.tile >= a.ntiles) return;
-  const int tx0 = (tid_.tile % a.ntx) * 16, ty0 = (tid_.tile / a.ntx) * ROWS;
-  const int cob = tid_.cob, n = blockIdx.z;
-  const float* x = static_cast<const float*>(a.x);
-  const float* x2 = static_cast<const float*>(a.x2);
-  const float* wp = static_cast<const float*>(a.wp);
-  const int Cin = a.Cx + a.C2;
-  // This thread stages channel group g (4 channels) of tile pixel 16 w + l % 16 + 64 k, g = l / 16
-  // (lane l of wave w; bank-conflict-free writes as in k_conv_lds; offsets in floats).
-  const int g4 = ((tid >> 4) & 3) * 4;
-  const int pl = (tid >> 6) * 16 + (tid & 15);
-  uint32_t xo[NXT], so[MODE == APS_CONV_UP2_CAT ? NXT : 1];
-#pragma unroll
-  for (int k = 0; k < NXT; ++k) {
-    const int p = pl + 64 * k, r = p / SW, col = p - r * SW;
-    const int iy = ty0 - 1 + r, ix = tx0 - 1 + col;
-    const bool in = p < SH * SW && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
-    uint32_t o = kNoPixel;
-    if (in) {
-      if constexpr (MODE == APS_CONV_POOL2)
-        o = (uint32_t)((((size_t)n * 2 * a.H + 2 * iy) * (2 * a.W) + 2 * ix) * a.Cx + g4);
-      else if constexpr (MODE == APS_CONV_UP2_CAT)
-        o = (uint32_t)((((size_t)n * (a.H / 2) + iy / 2) * (a.W / 2) + ix / 2) * a.Cx + g4);
-      else
-        o = (uint32_t)((((size_t)n * a.H + iy) * a.W + ix) * a.Cx + g4);
-    }
-    xo[k] = o;
-    if constexpr (MODE == APS_CONV_UP2_CAT)
-      so[k] = in ? (uint32_t)((((size_t)n * a.H + iy) * a.W + ix) * a.C2 + g4) : kNoPixel;
-  }
-  const uint32_t wo = (uint32_t)((((size_t)cob * TM * 9 + wave) * a.nchunk) * 256 + lane * 4);
-  const uint32_t wstep = (uint32_t)(4 * a.nchunk * 256);
-
-  f32x4 px[NXT], pa[NAT];  // clang vector types: HIP's struct vectors are not promoted here
-  uint32_t okbits = 0;
-  const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto fetch = [&](int c) {
-    const int cb = c * KC;
-    const bool in_ch = cb + g4 < Cin;
-    okbits = 0;
-#pragma unroll
-    for (int k = 0; k < NXT; ++k) {
-      const bool ok = xo[k] != kNoPixel && in_ch;
-      okbits |= (uint32_t)ok << k;
-      if constexpr (MODE == APS_CONV_DIRECT) {
-        px[k] = *reinterpret_cast<const f32x4*>(x + (ok ? xo[k] + cb : 0u));
-      } else if constexpr (MODE == APS_CONV_UP2_CAT) {
-        const float* src = cb + g4 < a.Cx ? x + (xo[k] + cb) : x2 + (so[k] + (cb - a.Cx));
-        px[k] = *reinterpret_cast<const f32x4*>(ok ? src : x);
-      } else {
-        f32x4 v = zero4;
-        if (ok) {
-          if constexpr (MODE == kModeReluMask) {
-            const f32x4 gr = *reinterpret_cast<const f32x4*>(x + (xo[k] + cb));
-            const f32x4 yv = *reinterpret_cast<const f32x4*>(x2 + (xo[k] + cb));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = yv[q] > 0.f ? gr[q] : 0.f;
-          } else {  // APS_CONV_POOL2
-            const uint32_t rs = (uint32_t)(2 * a.W * a.Cx);
-            const uint32_t o = xo[k] + cb;
-            const f32x4 q0 = *reinterpret_cast<const f32x4*>(x + o);
-            const f32x4 q1 = *reinterpret_cast<const f32x4*>(x + (o + a.Cx));
-            const f32x4 q2 = *reinterpret_cast<const f32x4*>(x + (o + rs));
-            const f32x4 q3 = *reinterpret_cast<const f32x4*>(x + (o + rs + a.Cx));
-            v = ((q0 + q1) + (q2 + q3)) * 0.25f;
-          }
-        }
-        px[k] = v;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NAT; ++k)
-      pa[k] = *reinterpret_cast<const f32x4*>(wp + ((tid + 256 * k < NAV ? wo + k * wstep : wo) + c * 256));
-  };
-  auto put = [&]() {
-#pragma unroll
-    for (int k = 0; k < NXT; ++k) {
-      const int p = pl + 64 * k;
-      if (p < SH * SW) *reinterpret_cast<f32x4*>(Xs + p * PS + g4) = (okbits >> k) & 1u ? px[k] : zero4;
-    }
-#pragma unroll
-    for (int k = 0; k < NAT; ++k) {
-      const int v = tid + 256 * k;
-      if (v < NAV) *reinterpret_cast<f32x4*>(As + v * 4) = pa[k];
-    }
-  };
-
-  f32x4 acc[TM][TN];
-#pragma unroll
-  for (int m = 0; m < TM; ++m) {
-    f32x4 b0 = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int co0 = (cob * TM + m) * 16 + 4 * (lane >> 4);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (a.bias && co0 + q < a.Cout) b0[q] = a.bias[co0 + q];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[m][j] = b0;
-  }
-
-  fetch(0);
-  put();
-  __syncthreads();
-  for (int c = 0; c < a.nchunk; ++c) {
-    const bool more = c + 1 < a.nchunk;
-    if (more) fetch(c + 1);
-    if constexpr (MODE == APS_CONV_POOL2 || MODE == kModeReluMask) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx) {
-      __builtin_amdgcn_sched_barrier(0);
-      f32x4 A[3][TM];
-#pragma unroll
-      for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-        for (int m = 0; m < TM; ++m) A[dy][m] = *reinterpret_cast<const f32x4*>(As + ((m * 9 + dy * 3 + dx) * 64 + lane) * 4);
-#pragma unroll
-      for (int ir = 0; ir < TN + 2; ++ir) {
-        const f32x4 B = *reinterpret_cast<const f32x4*>(Xs + ((wave * TN + ir) * SW + (lane & 15) + dx) * PS + (lane >> 4) * 4);
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-          const int j = ir - dy;
-          if (j >= 0 && j < TN) {
-#pragma unroll
-            for (int m = 0; m < TM; ++m) acc[m][j] = mma4(A[dy][m], B, acc[m][j]);
-          }
-        }
-      }
-    }
-    if (more) {
-      __syncthreads();
-      put();
-      __syncthreads();
-    }
-  }
-  if constexpr (HEAD) {
-    __syncthreads();  // the head's re-layout reuses Xs
-    conv_epilogue<float, float, TM, TN, HEAD, true>(a, acc, ty0 + wave * TN, tx0, cob, n, lane, wave, Xs);
-  } else {
-    lds_epilogue_f32<TM, TN>(a, acc, ty0 + wave * TN, tx0, cob, n, lane);
-  }
-}
-
-template <int MODE, int HEAD>
-void launch_conv_lds_f32_m(const ConvArgs& a, hipStream_t st) {
-  ConvArgs b = a;
-  b.ntx = (a.W + 15) / 16;
-  b.nchunk = (a.Cx + a.C2 + 15) / 16;
-  // 8-row blocks (TN = 2) for small problems, and for POOL2 with TM = 4, whose 16-row variant
-  // does not fit in 256 VGPRs
-  const bool wide = a.Cout > 32;
-  const bool tn2 = (size_t)a.N * a.H * a.W < 64 * 64 * 8 || (wide && MODE == APS_CONV_POOL2);
-  const int rows = tn2 ? 8 : 16;
-  b.ntiles = b.ntx * ((a.H + rows - 1) / rows);
-  b.nco = wide ? (a.Cout + 63) / 64 : 1;
-  dim3 grid(xcd_grid(b.ntiles, b.nco), 1, a.N);
-  if (!wide) {
-    if (tn2) k_conv_lds_f32<MODE, 2, 2, HEAD><<<grid, 256, 0, st>>>(b);
-    else k_conv_lds_f32<MODE, 2, 4, HEAD><<<grid, 256, 0, st>>>(b);
-  } else if (tn2) {
-    k_conv_lds_f32<MODE, 4, 2, HEAD><<<grid, 256, 0, st>>>(b);
-  } else if constexpr (MODE != APS_CONV_POOL2) {
-    k_conv_lds_f32<MODE, 4, 4, HEAD><<<grid, 256, 0, st>>>(b);
-  }
-}
-
-// Every fp32 3x3 convolution with more than 16 input channels (its weights are packed in
-// 16-channel chunks, which only this kernel reads).  false: 32-bit offsets would overflow.
-bool launch_conv_sweep_f32(const ConvArgs& a, hipStream_t st);  // the row sweep, below
-
-template <int HEAD>
-bool launch_conv_lds_f32(const ConvArgs& a, hipStream_t st) {
-  const size_t px = (size_t)a.N * a.H * a.W;
-  const size_t ex = a.mode == APS_CONV_POOL2 ? 4 * px * a.Cx
-                    : a.mode == APS_CONV_UP2_CAT ? px / 4 * a.Cx : px * a.Cx;
-  const size_t e2 = a.mode == APS_CONV_UP2_CAT ? px * a.C2 : 0;
-  if ((ex > e2 ? ex : e2) + 16 >= ((size_t)1 << 31)) return false;
-  if constexpr (HEAD) {
-    if (a.mode != APS_CONV_DIRECT) return false;
-    launch_conv_lds_f32_m<APS_CONV_DIRECT, HEAD>(a, st);
-    return true;
-  } else {
-    if (launch_conv_sweep_f32(a, st)) return true;
-    switch (a.mode) {
-      case APS_CONV_DIRECT: launch_conv_lds_f32_m<APS_CONV_DIRECT, 0>(a, st); return true;
-      case APS_CONV_POOL2: launch_conv_lds_f32_m<APS_CONV_POOL2, 0>(a, st); return true;
-      case APS_CONV_UP2_CAT: launch_conv_lds_f32_m<APS_CONV_UP2_CAT, 0>(a, st); return true;
-      case kModeReluMask: launch_conv_lds_f32_m<kModeReluMask, 0>(a, st); return true;
-      default: return false;
-    }
-  }
-}
-
 // Launch k_conv_lds for a bf16 3x3 convolution with bf16 output whose input channels fill
 // 32-channel chunks (Cin > 16); TM = 2 for Cout <= 32, else 4 with ceil(Cout / 64) channel
 // blocks; 8-row blocks for small problems.
@@ -1219,201 +639,6 @@ bool launch_conv_sweep(const ConvArgs& a, hipStream_t st) {
   return true;
 }
 
-// ---- fp32 form of the row sweep ------------------------------------------------------------
-// The same per-wave sweep for the fp32 networks' 32-channel full-resolution layers (16 or 32
-// input channels, 32 outputs, no head) and the half-resolution 32 -> 64 layer.  On the tiled fp32
-// kernel these run at 57-70 % of the MFMA peak against 81-87 % for the wider layers, each block
-// computing two 16-channel chunks at most for one staged tile.  Here the weights (9 taps x CH
-// chunks of 16 channels for MS m-tiles: both with 16 input channels; with 32 one per wave, its
-// neighbour waves taking the others, so that two waves fit a SIMD) stay in registers and each
-// input row is read from HBM once per band into a ring of three LDS rows, each held as CH planes
-// of [36 px][20 floats] (the tiled kernel's 80-byte pixel pitch, so the 16 lanes of a B read hit
-// distinct banks).  Output row o is summed in the tiled kernel's order: 16-channel chunks outer,
-// then taps dx, dy, four K = 4 MFMAs per tap, from the bias; so the two kernels give the same
-// bits.  Epilogue as lds_epilogue_f32: ReLU, 16-byte stores per lane, and with a pooled output
-// the 2x2 mean of the previous and the current row (neighbour column by DPP) in the POOL2 order.
-// Ring row i + 3 is staged into the slot of row i after this step's reads of it (one wave's LDS
-// operations complete in program order).
-constexpr int kCsfPS = 20;       // floats per staged pixel of a 16-channel plane
-
-template <int CH, int MS>
-__global__ __launch_bounds__(256) void k_conv_sweep_f32(ConvArgs a, int R, int nseg, int nunit) {
-  constexpr int PL = kCsPix * kCsfPS;           // floats of one plane of a ring row
-  constexpr int XR = CH * PL, XN = 3 * XR;      // ring of three rows
-  constexpr int NU = 34 * CH * 4;               // 16-byte units of an input row (34 pixels)
-  constexpr int NLD = (NU + 63) / 64;
-  constexpr int D = 2;                          // input rows in flight in registers
-  __shared__ __attribute__((aligned(16))) float lds[4][XN];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int unit = blockIdx.x * 4 + wave, n = blockIdx.y;
-  if (unit >= nunit) return;  // the whole wave; nothing below synchronises waves
-  const int H = a.H, W = a.W, Cx = a.Cx;
-  // MS = 1: the Cout / 16 m-tiles of a band segment go to neighbouring waves
-  const int nm = a.Cout >> 4;
-  const int mt0 = MS == 2 ? 0 : unit % nm, bs = MS == 2 ? unit : unit / nm;
-  const int x0 = (bs / nseg) * kCsCols, y0 = (bs % nseg) * R;
-  float* X = lds[wave];
-  for (int e = lane * 4; e < XN; e += 256) *reinterpret_cast<f32x4*>(X + e) = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // weights (16-channel chunk packing): fragment (m, tap, chunk c), lane l = output channel
-  // 16 m + l % 16, input channels 16 c + 4 (l / 16) + [0, 4)
-  const float* wp = static_cast<const float*>(a.wp);
-  f32x4 w[MS][9][CH];
-#pragma unroll
-  for (int m = 0; m < MS; ++m)
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-        w[m][t][c] = *reinterpret_cast<const f32x4*>(wp + ((size_t)(((mt0 + m) * 9 + t) * CH + c) * 64 + lane) * 4);
-  f32x4 bias[MS];
-#pragma unroll
-  for (int m = 0; m < MS; ++m) bias[m] = *reinterpret_cast<const f32x4*>(a.bias + 16 * (mt0 + m) + 4 * (lane >> 4));
-  int bo[2][3];  // B read offsets within a plane: pixel 16 s + l % 16 + dx, channels 4 (l / 16)
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx) bo[s][dx] = (16 * s + (lane & 15) + dx) * kCsfPS + 4 * (lane >> 4);
-
-  // input rows: unit u = lane + 64 k is pixel u / (4 CH) (column x0 - 1 + u / (4 CH)), chunk
-  // (u % (4 CH)) / 4, channels 4 (u % 4) .. + 3 of it
-  const uint32_t img_bytes = (uint32_t)((size_t)H * W * Cx * sizeof(float));
-  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(static_cast<const float*>(a.x) + (size_t)n * H * W * Cx), 0, img_bytes, 0x00020000);
-  auto load_row = [&](int iy, f32x4 (&v)[NLD]) {
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int u = lane + 64 * k, px = u / (4 * CH), xc = x0 - 1 + px;
-      const bool in = u < NU && iy >= 0 && iy < H && xc >= 0 && xc < W;
-      const uint32_t off = in ? (uint32_t)((((size_t)iy * W + xc) * Cx + 4 * (u % (4 * CH))) * sizeof(float)) : img_bytes;
-      v[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-    }
-  };
-  auto store_row = [&](float* dst, const f32x4 (&v)[NLD]) {
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int u = lane + 64 * k, px = u / (4 * CH), wv = u % (4 * CH);
-      if (u < NU) *reinterpret_cast<f32x4*>(dst + (wv >> 2) * PL + px * kCsfPS + 4 * (wv & 3)) = v[k];
-    }
-  };
-  float* y = static_cast<float*>(a.y);
-  float* yp = static_cast<float*>(a.pool);
-  const int ylast = min(y0 + R, H) - 1;
-  f32x4 hprev[2][MS];  // the previous (even) row's outputs, for the pooled copy
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int m = 0; m < MS; ++m) hprev[s][m] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto emit = [&](const f32x4 (&acc)[2][MS], int o) {
-    const bool second = (o - y0) & 1;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int col = x0 + 16 * s + (lane & 15);
-#pragma unroll
-      for (int m = 0; m < MS; ++m) {
-        const int co = 16 * (mt0 + m) + 4 * (lane >> 4);
-        f32x4 v = acc[s][m];
-        if (a.relu) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q], 0.f);
-        }
-        if (col < W) *reinterpret_cast<f32x4*>(y + (((size_t)n * H + o) * W + col) * a.ldy + co) = v;
-        if (yp) {
-          if (second) {
-            f32x4 nb0, nb1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              nb0[q] = lane_xor1(hprev[s][m][q]);
-              nb1[q] = lane_xor1(v[q]);
-            }
-            if ((lane & 1) == 0 && col < W)
-              *reinterpret_cast<f32x4*>(yp + (((size_t)n * (H / 2) + o / 2) * (W / 2) + col / 2) * a.Cout + co) =
-                  ((hprev[s][m] + nb0) + (v + nb1)) * 0.25f;
-          } else {
-            hprev[s][m] = v;
-          }
-        }
-      }
-    }
-  };
-
-  // ring row k (input row y0 - 1 + k) sits in slot k % 3; rows 0..2 are staged up front and rows
-  // 3, 4 wait in registers gx[k % 2]
-  {
-    f32x4 v[NLD];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      load_row(y0 - 1 + k, v);
-      store_row(X + k * XR, v);
-    }
-  }
-  f32x4 gx[D][NLD];
-#pragma unroll
-  for (int k = 3; k < 3 + D; ++k) load_row(y0 - 1 + k, gx[k % D]);
-
-  int s0 = 0;  // slot of ring row i
-  auto step = [&](auto ph, int i) {
-    constexpr int G = (decltype(ph)::value + 3) % D;  // == (i + 3) % D
-    const int s1 = s0 == 2 ? 0 : s0 + 1, s2 = s1 == 2 ? 0 : s1 + 1;
-    const float* rows[3] = {X + s0 * XR, X + s1 * XR, X + s2 * XR};
-    wave_lds_sync();
-    f32x4 acc[2][MS];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int m = 0; m < MS; ++m) acc[s][m] = bias[m];
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        __builtin_amdgcn_sched_barrier(0);  // one tap column's operands live at a time
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const f32x4 b = *reinterpret_cast<const f32x4*>(rows[dy] + c * PL + bo[s][dx]);
-#pragma unroll
-            for (int m = 0; m < MS; ++m) acc[s][m] = mma4(w[m][3 * dy + dx][c], b, acc[s][m]);
-          }
-      }
-    wave_lds_sync();
-    const int o = y0 + i;
-    if (o <= ylast) emit(acc, o);
-    store_row(X + s0 * XR, gx[G]);  // ring row i + 3 into the slot of row i
-    load_row(y0 + 2 + i + D, gx[G]);
-    s0 = s1;
-  };
-  for (int i = 0; i < R; i += 4) {  // R % 4 == 0 (host)
-    step(std::integral_constant<int, 0>{}, i);
-    step(std::integral_constant<int, 1>{}, i + 1);
-    step(std::integral_constant<int, 2>{}, i + 2);
-    step(std::integral_constant<int, 3>{}, i + 3);
-  }
-}
-
-// false: not this kernel's configuration (fp32 3x3 direct, no head: 32 outputs from 16 or 32
-// inputs, 64 from 32)
-bool launch_conv_sweep_f32(const ConvArgs& a, hipStream_t st) {
-  if (a.mode != APS_CONV_DIRECT || a.C2 != 0 || a.ldy != a.Cout || a.hw || a.hside || !a.bias ||
-      !((a.Cout == 32 && (a.Cx == 16 || a.Cx == 32)) || (a.Cout == 64 && a.Cx == 32)))
-    return false;
-  if (a.pool && (a.H % 2 || a.W % 2)) return false;
-  if ((size_t)a.H * a.W * a.Cx * 4 >= (1ull << 31) || a.N > 65535) return false;
-  const long nband = (a.W + kCsCols - 1) / kCsCols;
-  // with 32 input channels each wave takes one m-tile (the weights of two would leave one wave
-  // per SIMD), its neighbours the others; the launch aims at about 2048 waves, two per SIMD
-  const int wps = a.Cx == 32 ? a.Cout / 16 : 1;  // waves per band segment
-  long R = std::max<long>(8, ((long)a.N * a.H * nband * wps + 2047) / 2048);
-  R = (std::min<long>(R, a.H) + 3) / 4 * 4;  // four steps per loop iteration
-  const int nseg = (int)((a.H + R - 1) / R);
-  const long nunit = nband * nseg * wps;
-  if (nunit > (1L << 30) / 4) return false;
-  dim3 g((unsigned)((nunit + 3) / 4), a.N);
-  if (a.Cx == 32) k_conv_sweep_f32<2, 1><<<g, 256, 0, st>>>(a, (int)R, nseg, (int)nunit);
-  else k_conv_sweep_f32<1, 2><<<g, 256, 0, st>>>(a, (int)R, nseg, (int)nunit);
-  return true;
-}
-
 // false: the configuration is not covered (the caller uses k_conv)
 template <int HEAD>
 bool launch_conv_lds(const ConvArgs& a, hipStream_t st) {
@@ -1479,28 +704,7 @@ __global__ void k_pack(const float* __restrict__ w, int Cout, int KS, int Cin, i
   else out[i] = v;
 }
 
-// fp32 3x3 layers with more than 16 input channels (the operand of k_conv_lds_f32), in chunks of
-// 16 channels with 4 per lane:
-// packed[(((ct * 9 + tap) * nchunk16 + c) * 64 + lane) * 4 + e] =
-//     w[co = 16 ct + lane % 16][tap][ci = 16 c + 4 (lane / 16) + e]   (0 outside)
-// (transpose as in k_pack).
-__global__ void k_pack_f32c16(const float* __restrict__ w, int Cout, int Cin, int nchunk16,
-                              size_t total, float* __restrict__ out, int transpose) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int e = (int)(i & 3), lane = (int)((i >> 2) & 63);
-  size_t r = i >> 8;
-  const int c = (int)(r % nchunk16);
-  r /= nchunk16;
-  const int tap = (int)(r % 9), ct = (int)(r / 9);
-  const int co = ct * 16 + (lane & 15), ci = c * 16 + (lane >> 4) * 4 + e;
-  float v = 0.f;
-  if (co < Cout && ci < Cin)
-    v = transpose ? w[((size_t)ci * 9 + (8 - tap)) * Cout + co] : w[((size_t)co * 9 + tap) * Cin + ci];
-  out[i] = v;
-}
-
-// fp32 3x3 convolutions with more than 16 input channels run only in k_conv_lds_f32, which
+// fp32 3x3 convolutions in 32-channel chunks run only in k_conv_split (conv_f32.hip), which
 // addresses its inputs with 32-bit element offsets
 bool fp32_offsets_fit(int mode, int N, int H, int W, int Cx, int C2) {
   const size_t px = (size_t)N * H * W;
@@ -1509,8 +713,7 @@ bool fp32_offsets_fit(int mode, int N, int H, int W, int Cx, int C2) {
   return (ex > e2 ? ex : e2) + 16 < ((size_t)1 << 31);
 }
 
-// 8-channel groups of the K layout (see k_conv).  4: 32-channel chunks (fp32: the 16-channel
-// chunks of k_conv_lds_f32), for 1x1 convolutions, 3x3 with more than 16 input channels, and
+// 8-channel groups of the K layout (see k_conv).  4: 32-channel chunks, for 1x1 convolutions, 3x3 with more than 16 input channels, and
 // 3x3 with 9..16 input channels whose output channels fill whole 16-channel tiles beyond 16 (the
 // U-Net's first layer: it runs in the LDS kernels, in bf16 as one half-filled chunk).  1 or 2:
 // merged (tap, group) pairs for the other 3x3 layers with <= 16 input channels (the sampler).
@@ -1545,11 +748,7 @@ void launch_conv(const ConvArgs& a, hipStream_t st) {
 // epilogue.
 template <typename T, int TM, int HM>
 void launch_conv_head_hm(const ConvArgs& a, hipStream_t st) {
-  if constexpr (sizeof(T) == 2) {
-    if (launch_conv_lds<HM>(a, st)) return;
-  } else {
-    if (launch_conv_lds_f32<HM>(a, st)) return;
-  }
+  if (launch_conv_lds<HM>(a, st)) return;
   const bool big = (size_t)a.H * a.W >= 64 * 64;
   const int TN = big ? 4 : 2, TH = 4 * TN;
   ConvArgs b = a;
@@ -1687,7 +886,7 @@ void dispatch_tiles(const ConvArgs& a, hipStream_t st) {
     if (launch_conv_lds<false>(a, st)) return;
   }
   if constexpr (sizeof(T) == 4 && KS == 3 && CG == 4) {
-    launch_conv_lds_f32<false>(a, st);  // sizes checked by the entry points (fp32_offsets_fit)
+    conv_split(a, st);  // sizes checked by the entry points (fp32_offsets_fit)
     return;
   }
   const bool big = (size_t)a.H * a.W >= 64 * 64;
@@ -2008,11 +1207,8 @@ static int pack_impl(const float* w, int Cout, int ksize, int Cin, int dtype, vo
   const int blocks = (int)((total + 255) / 256);
   hipStream_t st = as_stream(stream);
   if (dtype == APS_F32 && ksize == 3 && conv_cg(3, ci, co) == 4) {
-    // 16-channel chunks (fits in the packed_elems allocation, which counts 32-channel chunks)
-    const int n16 = (ci + 15) / 16;
-    const size_t t16 = (size_t)((co + 16 * kMaxTM - 1) / (16 * kMaxTM)) * kMaxTM * 9 * n16 * 256;
-    k_pack_f32c16<<<(int)((t16 + 255) / 256), 256, 0, st>>>(w, co, ci, n16, t16,
-                                                            static_cast<float*>(packed), transpose);
+    // two halves per weight: the same bytes as one float
+    pack_split(w, co, ci, packed, transpose, st);
   } else if (dtype == APS_F32)
     k_pack<float><<<blocks, 256, 0, st>>>(w, co, ksize, ci, nchunk, total,
                                           static_cast<float*>(packed), transpose, conv_cg(ksize, ci, co));
@@ -2110,9 +1306,9 @@ int aps_conv2d_bwd_data(const void* dy, const void* ymask, int ldy, int N, int H
   a.bias = nullptr;
   a.Cout = Cin;
   a.nchunk = (ldy + kChunk - 1) / kChunk;
+  a.cvalid = Cout;
   // the operator was packed for Cout input channels: the padded stride must give the same layout
-  const int kc = dtype == APS_F32 && ksize == 3 && conv_cg(3, ldy, Cin) == 4 ? 16 : kChunk;
-  if ((ldy + kc - 1) / kc != (Cout + kc - 1) / kc || conv_cg(ksize, ldy, Cin) != conv_cg(ksize, Cout, Cin))
+  if ((ldy + kChunk - 1) / kChunk != (Cout + kChunk - 1) / kChunk || conv_cg(ksize, ldy, Cin) != conv_cg(ksize, Cout, Cin))
     return APS_ERR_SHAPE;
   if (dtype == APS_F32 && ksize == 3 && conv_cg(3, ldy, Cin) == 4 &&
       !fp32_offsets_fit(a.mode == kModeReluMask ? APS_CONV_DIRECT : a.mode, N, H, W, ldy, 0))
@@ -2279,7 +1475,8 @@ int aps_conv2d_fwd_pool(const void* x, const void* x2, int N, int H, int W, int 
   a.relu = relu;
   a.pool = pooled;
   if (dtype == APS_F32) {
-    if (!launch_conv_lds_f32<false>(a, as_stream(stream))) return APS_ERR_UNSUPPORTED;
+    if (!fp32_offsets_fit(mode, N, H, W, Cx, C2)) return APS_ERR_UNSUPPORTED;
+    conv_split(a, as_stream(stream));
   } else if (!launch_conv_lds<false>(a, as_stream(stream))) {
     return APS_ERR_UNSUPPORTED;
   }
@@ -2351,7 +1548,7 @@ int aps_conv2d_fwd_head_ex(const void* x, const void* x2, int N, int H, int W, i
   hipStream_t st = as_stream(stream);
   if (dtype == APS_F32 && !fp32_offsets_fit(mode, N, H, W, Cx, C2)) return APS_ERR_UNSUPPORTED;
   if (dtype == APS_F32) {
-    if (Cout == 32) launch_conv_head<float, 2>(a, st); else launch_conv_head<float, 4>(a, st);
+    conv_split(a, st);
   } else if (dtype == APS_BF16) {
     if (Cout == 32) launch_conv_head<uint16_t, 2>(a, st); else launch_conv_head<uint16_t, 4>(a, st);
   } else {
