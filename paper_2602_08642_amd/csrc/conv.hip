@@ -117,9 +117,80 @@ constexpr uint32_t kNoPixel = 0xffffffffu;
 // bf16 y > 0 (positive, finite or +inf), decided on the bits
 __device__ inline bool bf_pos(uint16_t b) { return (int16_t)b > 0 && (b & 0x7fffu) <= 0x7f80u; }
 
+// Orders this wave's LDS accesses across lanes: a compiler barrier for memory operations (the
+// LDS itself completes one wave's operations in program order).  Plain signal fences are not
+// enough where the two sides use different vector types, which type-based alias analysis may
+// then take as disjoint.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Stores a wave's TN rows x 16 px x 16 TM channels: rounded to bf16, ReLU on the rounded bits
+// (round-to-nearest-even keeps the sign, so this equals rounding max(v, 0)).  A lane holds 4
+// channels of a pixel and its neighbours the same channels of other pixels, so stored as they are
+// every lane opens another cache line; two rows at a time go through st, a region of this wave of
+// 32 px x 16 TM elements, and leave as 16-byte runs of channels, consecutive lanes to consecutive
+// addresses.  Cout % 16 == 0 and ldy % 4 == 0 (host).  With a.pool, the 2x2 means of the stored
+// values, summed in the order of the POOL2 input transform, go to the half-resolution tensor; H, W
+// and the tile origins are even.
+template <int TM, int TN>
+__device__ inline void store_tile(const ConvArgs& a, const f32x4 (&acc)[TM][TN], int row0, int tx0,
+                                  int cob, int n, int lane, uint16_t* st) {
+  constexpr int VP = 2 * TM;  // 8-channel vectors per pixel, permuted by the pixel's column
+  auto at = [st](int p, int v) { return st + (p * VP + (v ^ (TM == 4 ? p & 7 : (p >> 1) & 3))) * 8; };
+  uint16_t* y = static_cast<uint16_t*>(a.y);
+  uint16_t* yp = static_cast<uint16_t*>(a.pool);
+  const bool v16 = (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
+#pragma unroll
+  for (int j0 = 0; j0 < TN; j0 += 2) {
+    if (j0) wave_lds_sync();
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+      for (int m = 0; m < TM; ++m) {
+        const f32x4 r = acc[m][j0 + jj];
+        s16x4 h = __builtin_bit_cast(s16x4, f2bf4(r[0], r[1], r[2], r[3]));
+        if (a.relu) h = __builtin_elementwise_max(h, s16x4{0, 0, 0, 0});
+        *reinterpret_cast<s16x4*>(at(jj * 16 + (lane & 15), 2 * m + (lane >> 5)) + 4 * ((lane >> 4) & 1)) = h;
+      }
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < TM; ++k) {
+      const int i = lane + 64 * k, p = i / VP, v = i % VP;
+      const int row = row0 + j0 + (p >> 4), col = tx0 + (p & 15), co = cob * TM * 16 + v * 8;
+      const u16x8 h = *reinterpret_cast<const u16x8*>(at(p, v));
+      if (row < a.H && col < a.W && co < a.Cout) {
+        uint16_t* d = y + (((size_t)n * a.H + row) * a.W + col) * a.ldy + co;
+        if (v16) {
+          *reinterpret_cast<u16x8*>(d) = h;
+        } else {
+          *reinterpret_cast<u16x4*>(d) = u16x4{h[0], h[1], h[2], h[3]};
+          *reinterpret_cast<u16x4*>(d + 4) = u16x4{h[4], h[5], h[6], h[7]};
+        }
+      }
+    }
+    if (yp) {
+      const int i = lane, p = i / VP, v = i % VP;  // 8 pooled pixels x VP vectors <= 64 lanes
+      const int row = row0 + j0, col = tx0 + 2 * p, co = cob * TM * 16 + v * 8;
+      if (p < 8 && row < a.H && col < a.W && co < a.Cout) {
+        const V8f q0 = load8(at(2 * p, v)), q1 = load8(at(2 * p + 1, v)), q2 = load8(at(16 + 2 * p, v)),
+                  q3 = load8(at(17 + 2 * p, v));
+        float r[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = ((q0.v[e] + q1.v[e]) + (q2.v[e] + q3.v[e])) * 0.25f;
+        const u16x4 lo = f2bf4(r[0], r[1], r[2], r[3]), hi = f2bf4(r[4], r[5], r[6], r[7]);
+        *reinterpret_cast<u16x8*>(yp + (((size_t)n * (a.H / 2) + row / 2) * (a.W / 2) + col / 2) * a.Cout + co) =
+            u16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      }
+    }
+  }
+}
+
 template <int MODE, int TM, int TN, int HEAD>
 __global__ __launch_bounds__(256, 2) void k_conv_lds(ConvArgs a) {
-  constexpr int ROWS = 4 * TN, SH = ROWS + 2, SW = 18, PS = 40;
+  constexpr int ROWS = 4 * TN, SH = ROWS + 2, SW = 18, PS = 32;
   constexpr int NXV = SH * SW * 4, NXT = (NXV + 255) / 256;  // input 16-B vectors per chunk
   constexpr int NAV = TM * 9 * 64, NAT = (NAV + 255) / 256;  // weight 16-B vectors per chunk
   constexpr int XS_TILE = SH * SW * PS, XS_HEAD = HEAD ? head_lds_elems<uint16_t, uint16_t, TM, HEAD>() : 0;
@@ -135,15 +206,19 @@ __global__ __launch_bounds__(256, 2) void k_conv_lds(ConvArgs a) {
   const uint16_t* x2 = static_cast<const uint16_t*>(a.x2);
   const uint16_t* wp = static_cast<const uint16_t*>(a.wp);
   const int Cin = a.Cx + a.C2;
-  // This thread stages channel group g (8 channels) of tile pixels (tid / 4) + 64 k.  Their
+  // This thread stages channel group g = tid % 4 (8 channels) of tile pixels tid / 4 + 64 k.  Their
   // element offsets at chunk 0 are computed once (32-bit; kNoPixel outside the image):
   // xo into x (for POOL2 the top-left of the 2x2 window, for UP2_CAT the parent pixel of the
   // coarse tensor), so into the skip tensor x2 (UP2_CAT only).
-  // Lane l of wave w stages pixel 16 w + l % 16 (+ 64 k) and channel group l / 16: a 16-lane
-  // group writes 16 consecutive tile pixels at the padded pixel stride, which hits distinct LDS
-  // banks (four lanes per pixel at one stride would collide every fourth pixel).
-  const int g8 = ((tid >> 4) & 3) * 8;
-  const int pl = (tid >> 6) * 16 + (tid & 15);
+  // Four neighbouring lanes read one pixel's 64 bytes of the chunk and write them to the pixel's
+  // 64 bytes in LDS, whose 16-byte groups are permuted by the column (xoff): the reads are 64-byte
+  // runs (one lane per pixel opened a cache line per lane), the writes and the MFMA loop's reads of
+  // sixteen neighbouring pixels hit distinct banks without padding.  With the staged stores
+  // (store_tile), 1080p: 64 -> 64 at half size 53 -> 49 us, 128 -> 128 at a quarter 45 -> 42,
+  // 384 -> 128 111 -> 106; the 14 layers of the U-Net 832 -> 800.
+  const int g8 = (tid & 3) * 8;
+  const int pl = tid >> 2;
+  auto xoff = [](int row, int col, int g) { return (row * SW + col) * PS + ((g ^ ((col >> 1) & 3)) << 3); };
   uint32_t xo[NXT], so[MODE == APS_CONV_UP2_CAT ? NXT : 1];
 #pragma unroll
   for (int k = 0; k < NXT; ++k) {
@@ -222,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_lds(ConvArgs a) {
       const int p = pl + 64 * k;
       if (p < SH * SW) {
         const u16x8 v = (okbits >> k) & 1u ? px[k] : u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        *reinterpret_cast<u16x8*>(Xs + p * PS + g8) = v;
+        *reinterpret_cast<u16x8*>(Xs + xoff(p / SW, p % SW, g8 >> 3)) = v;
       }
     }
 #pragma unroll
@@ -262,7 +337,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_lds(ConvArgs a) {
 #pragma unroll
       for (int ir = 0; ir < TN + 2; ++ir) {
         Frag<uint16_t> B;
-        frag_load(B, Xs + ((wave * TN + ir) * SW + (lane & 15) + dx) * PS + (lane >> 4) * 8);
+        frag_load(B, Xs + xoff(wave * TN + ir, (lane & 15) + dx, lane >> 4));
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy) {
           const int j = ir - dy;
@@ -283,53 +358,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_lds(ConvArgs a) {
     __syncthreads();  // the head's re-layout reuses Xs
     conv_epilogue<uint16_t, uint16_t, TM, TN, HEAD, true>(a, acc, ty0 + wave * TN, tx0, cob, n, lane, wave, Xs);
   } else {
-    // bf16 store of 4 channels per lane; ReLU on the rounded bits (round-to-nearest-even keeps
-    // the sign, so this equals rounding max(v, 0)).  Cout % 16 == 0 and ldy % 4 == 0 (host).
-    // With a.pool, the 2x2 mean of the stored values (rows j, j+1 of this lane; columns of
-    // this lane and its neighbour lane ^ 1), summed in the order of the POOL2 input transform,
-    // goes to the half-resolution tensor; H, W and the tile origins are even.
-    uint16_t* y = static_cast<uint16_t*>(a.y);
-    uint16_t* yp = static_cast<uint16_t*>(a.pool);
-    const int col = tx0 + (lane & 15);
-#pragma unroll
-    for (int j0 = 0; j0 < TN; j0 += 2) {
-#pragma unroll
-      for (int m = 0; m < TM; ++m) {
-        const int co = (cob * TM + m) * 16 + 4 * (lane >> 4);
-        if (co >= a.Cout) continue;
-        s16x4 h[2];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const int j = j0 + jj, row = ty0 + wave * TN + j;
-          h[jj] = __builtin_bit_cast(s16x4, f2bf4(acc[m][j][0], acc[m][j][1], acc[m][j][2], acc[m][j][3]));
-          if (a.relu) h[jj] = __builtin_elementwise_max(h[jj], s16x4{0, 0, 0, 0});
-          if (row < a.H && col < a.W)
-            *reinterpret_cast<s16x4*>(y + (((size_t)n * a.H + row) * a.W + col) * a.ldy + co) = h[jj];
-        }
-        if (yp) {
-          // neighbour column's values (all lanes take part in the exchange)
-          s16x4 nb[2];
-#pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            const uint2 u = __builtin_bit_cast(uint2, h[jj]);
-            // DPP quad_perm [1,0,3,2]: lane l reads lane l ^ 1
-            nb[jj] = __builtin_bit_cast(
-                s16x4, make_uint2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.x, 0xB1, 0xF, 0xF, true),
-                                  (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.y, 0xB1, 0xF, 0xF, true)));
-          }
-          const int row = ty0 + wave * TN + j0;
-          if ((lane & 1) == 0 && row < a.H && col < a.W) {
-            float r[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              r[e] = ((bf2f((uint16_t)h[0][e]) + bf2f((uint16_t)nb[0][e])) +
-                      (bf2f((uint16_t)h[1][e]) + bf2f((uint16_t)nb[1][e]))) * 0.25f;
-            *reinterpret_cast<u16x4*>(yp + (((size_t)n * (a.H / 2) + row / 2) * (a.W / 2) + col / 2) * a.Cout + co) =
-                f2bf4(r[0], r[1], r[2], r[3]);
-          }
-        }
-      }
-    }
+    __syncthreads();  // the staging rows lie in As
+    store_tile<TM, TN>(a, acc, ty0 + wave * TN, tx0, cob, n, lane, As + wave * (32 * 16 * TM));
   }
 }
 
@@ -375,16 +405,6 @@ constexpr int kCsCols = 32;      // output columns per band (two 16-pixel n-tile
 constexpr int kCsPix = 36;       // staged input positions per row: 34 read + 2 zero (pad reads)
 constexpr long kCsWaves = 2048;  // waves per launch the band height aims at (two per SIMD)
 constexpr int kCsDepth = 4;      // input rows requested ahead, steps per loop iteration (R % 4 == 0)
-
-// Orders this wave's LDS accesses across lanes: a compiler barrier for memory operations (the
-// LDS itself completes one wave's operations in program order).  Plain signal fences are not
-// enough where the two sides use different vector types, which type-based alias analysis may
-// then take as disjoint.
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // element offset of 8-channel group g of staged pixel p (CG groups per pixel): 64-byte pixels
 // swizzle their chunks on pixel bits 1-2, 32-byte pixels on bit 2
