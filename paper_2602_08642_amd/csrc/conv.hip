@@ -403,7 +403,6 @@ void launch_conv_lds_m(const ConvArgs& a, hipStream_t st) {
 // staging rows; wave_lds_sync keeps the compiler from reordering them.
 constexpr int kCsCols = 32;      // output columns per band (two 16-pixel n-tiles)
 constexpr int kCsPix = 36;       // staged input positions per row: 34 read + 2 zero (pad reads)
-constexpr long kCsWaves = 2048;  // waves per launch the band height aims at (two per SIMD)
 constexpr int kCsDepth = 4;      // input rows requested ahead, steps per loop iteration (R % 4 == 0)
 
 // element offset of 8-channel group g of staged pixel p (CG groups per pixel): 64-byte pixels
@@ -643,18 +642,18 @@ bool launch_conv_sweep(const ConvArgs& a, hipStream_t st) {
   }
   if ((size_t)a.H * a.W * a.Cx * 2 >= (1ull << 31) || a.N > 65535) return false;
   const long nband = (a.W + kCsCols - 1) / kCsCols, halves = a.Cout / 32;
-  // rows per wave: a multiple of the prefetch depth (even, so pooled rows pair up in a segment)
-  long R = std::max<long>(8, ((long)a.N * a.H * nband * halves + kCsWaves - 1) / kCsWaves);
-  R = (std::min<long>(R, a.H) + kCsDepth - 1) / kCsDepth * kCsDepth;
-  const int nseg = (int)((a.H + R - 1) / R);
+  // rows per wave: a multiple of the prefetch depth (even, so pooled rows pair up in a segment);
+  // two halo rows and about ten steps' time to load the weights and the first rows
+  const SweepPlan plan = sweep_plan(a.N, a.H, nband * halves, kCsDepth, 12);
+  const long R = plan.R, nseg = plan.nseg;
   const long nunit = nband * nseg * halves;
   if (nunit > (1L << 30) / 4) return false;
   dim3 g((unsigned)((nunit + 3) / 4), a.N);
   if constexpr (HM == 0) {
-    if (a.Cx == 32) k_conv_sweep<4, 0><<<g, 256, 0, st>>>(a, (int)R, nseg, (int)nunit);
-    else k_conv_sweep<2, 0><<<g, 256, 0, st>>>(a, (int)R, nseg, (int)nunit);
+    if (a.Cx == 32) k_conv_sweep<4, 0><<<g, 256, 0, st>>>(a, (int)R, (int)nseg, (int)nunit);
+    else k_conv_sweep<2, 0><<<g, 256, 0, st>>>(a, (int)R, (int)nseg, (int)nunit);
   } else {
-    k_conv_sweep<4, HM><<<g, 256, 0, st>>>(a, (int)R, nseg, (int)nunit);
+    k_conv_sweep<4, HM><<<g, 256, 0, st>>>(a, (int)R, (int)nseg, (int)nunit);
   }
   return true;
 }

@@ -322,7 +322,12 @@ __global__ __launch_bounds__(256) void k_sampler_sweep(SamplerArgs a, int R, int
       acc2[k][s] = f32x4{0.f, 0.f, 0.f, 0.f};
       s3[k][s] = 0.f;
     }
-  float* zimg = a.z + (size_t)n * a.H * a.W + x0;
+  const __amdgpu_buffer_rsrc_t zb =
+      __builtin_amdgcn_make_buffer_rsrc(a.z + (size_t)n * a.H * a.W, 0, (uint32_t)a.H * a.W * 4, kBufferWord3);
+  constexpr uint32_t kNoStore = 0x80000000u;  // past the image (host: under 2^31 bytes)
+  uint32_t zo[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) zo[s] = zok[s] ? (uint32_t)(x0 + (lane & 15) + 16 * s) * 4 : kNoStore;
   const int ylast = min(y0 + R, a.H) - 1;  // last output row of this band segment
 
   // one step: input row I0 + i through layer 1, the row layer 1 wrote at step i - 1 through
@@ -374,13 +379,14 @@ __global__ __launch_bounds__(256) void k_sampler_sweep(SamplerArgs a, int R, int
     emit(acc2[C], lim2, I0 + i - 3, H2);
     const int oy = I0 + i - 5;
     const bool zrow = oy >= y0 && oy <= ylast;
-    float* zr = zimg + (size_t)oy * a.W;
+    const uint32_t zr = (uint32_t)oy * (uint32_t)(a.W * 4);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       s3[F][s] = c3[s][0];
       s3[M][s] += c3[s][1];
       const float zv = s3[C][s] + c3[s][2];
-      if (zrow && zok[s]) zr[(lane & 15) + 16 * s] = zv;
+      // through a resource over the image's z: no branch splits the step
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, zv), zb, zrow ? zr + zo[s] : kNoStore, 0, 0);
     }
     store_row(gx[G]);
     gx[G] = load_row(I0 + i + 1 + D);
@@ -420,12 +426,11 @@ int sampler_cnn(const void* x, int N, int H, int W, int C, int Cin, const void* 
   dim3 grid(a.ntx * ((H + 15) / 16), 1, N);
   const bool cg1 = Cin <= 8;
   if (dtype == APS_BF16) {
-    // row sweep: band segments of R rows, R chosen so that about kSweepWaves waves cover the
-    // images (all resident at once at two waves per SIMD)
-    constexpr long kSweepWaves = 2048;
+    // row sweep: eight steps more than rows, and about fifteen steps' time before the first.  With
+    // 2072 waves where 2048 are resident, 3840 x 2160 took 166 us; 1924 taller ones take 129.
     const long nband = (W + kSweepCols - 1) / kSweepCols;
-    const int R = (int)std::max<long>(8, ((long)N * H * nband + kSweepWaves - 1) / kSweepWaves);
-    const int nseg = (H + R - 1) / R;
+    const SweepPlan plan = sweep_plan(N, H, nband, 1, 23);
+    const int R = (int)plan.R, nseg = (int)plan.nseg;
     const long nunit = nband * nseg;
     // the buffer resource addresses one image with 32-bit byte offsets
     if (nunit > (1L << 30) / 4 || N > 65535 || (size_t)H * W * C * 2 >= (1ull << 31))
