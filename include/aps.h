@@ -108,6 +108,16 @@ int aps_conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, i
                    const void* packed_w, const float* bias, int Cout, int ksize, int relu,
                    int dtype, void* y, int ldy, int y_dtype, void* stream);
 
+/* The forward pass of a training layer with a ReLU, whose signs the backward pass uses: fp32 3x3
+ * layers in plain fp32 products (order: bias, 16-channel chunks, dx outer, dy inner), from weights
+ * packed by aps_conv_pack_weights_train (aps_conv_packed_elems elements); otherwise aps_conv2d_fwd
+ * and aps_conv_pack_weights. */
+int aps_conv_pack_weights_train(const float* w, int Cout, int ksize, int Cin, int dtype, void* packed,
+                                void* stream);
+int aps_conv2d_fwd_train(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,
+                         const void* packed_w, const float* bias, int Cout, int ksize, int relu,
+                         int dtype, void* y, int ldy, int y_dtype, void* stream);
+
 /* A 3x3 conv (input as aps_conv2d_fwd, dtype APS_BF16 or APS_F32 for inputs, weights and
  * outputs, Cx + C2 > 16, Cout a multiple of 16 and > 16, H and W even, output row stride Cout)
  * that also writes the 2x2 average pool of its output: pooled [N,H/2,W/2,Cout], equal bit for

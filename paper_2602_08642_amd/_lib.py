@@ -35,6 +35,8 @@ SIGNATURES = {
     "aps_status_string": (C.c_char_p, [I]),
     "aps_conv_packed_elems": (SZ, [I, I, I]),
     "aps_conv_pack_weights": (I, [P, I, I, I, I, P, P]),
+    "aps_conv_pack_weights_train": (I, [P, I, I, I, I, P, P]),
+    "aps_conv2d_fwd_train": (I, [P, P, I, I, I, I, I, I, P, P, I, I, I, I, P, I, I, P]),
     "aps_conv2d_fwd": (I, [P, P, I, I, I, I, I, I, P, P, I, I, I, I, P, I, I, P]),
     "aps_conv2d_fwd_head": (I, [P, P, I, I, I, I, I, I, P, P, I, I, P, P, I, I, P, I, P, I, P]),
     "aps_conv2d_fwd_head_ex": (I, [P, P, I, I, I, I, I, I, P, P, I, I, P, P, I, I, P, I, P, I, P, I, P]),

@@ -38,13 +38,23 @@ class LayerRef:
         ops.L.check(lib.aps_conv_pack_weights(ops._p(self.w.detach()), self.spec["cout"], self.spec["k"],
                                               self.spec["cin"], ops._dt(self.dtype), ops._p(self.packed),
                                               ops._stream()), "pack_weights")
+        # fp32 layers with a ReLU: the forward pass whose signs the backward pass uses has its own packing
+        self.packed_train = None
+        if self.dtype == F32 and self.spec["k"] == 3 and self.spec["relu"]:
+            self.packed_train = torch.empty_like(self.packed)
+            ops.L.check(lib.aps_conv_pack_weights_train(ops._p(self.w.detach()), self.spec["cout"], self.spec["k"],
+                                                        self.spec["cin"], ops._dt(self.dtype),
+                                                        ops._p(self.packed_train), ops._stream()),
+                        "pack_weights_train")
         self.packed_T = ops.pack_dgrad(self.spec, self.w.detach(), self.dtype)
 
 
 class Conv(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, x2, w, b, layer: LayerRef, mode: str, out_dtype, ldy):
-        y = ops.conv2d(x, layer.spec, layer.packed, b.detach(), mode, x2, out_dtype=out_dtype, ldy=ldy)
+        tr = layer.packed_train is not None and out_dtype in (None, F32)
+        y = ops.conv2d(x, layer.spec, layer.packed_train if tr else layer.packed, b.detach(), mode, x2,
+                       out_dtype=out_dtype, ldy=ldy, train=tr)
         ctx.layer, ctx.mode = layer, mode
         ctx.save_for_backward(x, x2, y)
         return y

@@ -1317,14 +1317,24 @@ int aps_conv_pack_weights(const float* w, int Cout, int ksize, int Cin, int dtyp
   return pack_impl(w, Cout, ksize, Cin, dtype, packed, stream, 0);
 }
 
+int aps_conv_pack_weights_train(const float* w, int Cout, int ksize, int Cin, int dtype, void* packed,
+                                void* stream) {
+  if (dtype != APS_F32 || ksize != 3 || Cout <= 0 || Cin <= 0 || conv_cg(3, Cin, Cout) != 4)
+    return pack_impl(w, Cout, ksize, Cin, dtype, packed, stream, 0);
+  if (!w || !packed) return APS_ERR_NULL;
+  pack_f32c16(w, Cout, Cin, packed, as_stream(stream));
+  APS_LAUNCH_CHECK();
+  return APS_OK;
+}
+
 int aps_conv_pack_weights_dgrad(const float* w, int Cout, int ksize, int Cin, int dtype,
                                 void* packed, void* stream) {
   return pack_impl(w, Cout, ksize, Cin, dtype, packed, stream, 1);
 }
 
-int aps_conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,
+static int conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,
                    const void* packed_w, const float* bias, int Cout, int ksize, int relu,
-                   int dtype, void* y, int ldy, int y_dtype, void* stream) {
+                   int dtype, void* y, int ldy, int y_dtype, void* stream, bool train) {
   if (N < 0 || H < 0 || W < 0 || Cx <= 0 || C2 < 0 || Cout <= 0) return APS_ERR_SHAPE;
   if ((size_t)N * H * W == 0) return APS_OK;
   if (!x || !packed_w || !bias || !y) return APS_ERR_NULL;
@@ -1360,12 +1370,27 @@ int aps_conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, i
   if (dtype == APS_F32 && ksize == 3 && conv_cg(3, Cx + C2, Cout) == 4 &&
       !fp32_offsets_fit(mode, N, H, W, Cx, C2))
     return APS_ERR_UNSUPPORTED;
-  if (dtype == APS_F32 && y_dtype == APS_F32) dispatch_ks<float, float>(a, ksize, st);
+  if (train && dtype == APS_F32 && y_dtype == APS_F32 && ksize == 3 && conv_cg(3, Cx + C2, Cout) == 4) conv_f32(a, st);
+  else if (dtype == APS_F32 && y_dtype == APS_F32) dispatch_ks<float, float>(a, ksize, st);
   else if (dtype == APS_BF16 && y_dtype == APS_BF16) dispatch_ks<uint16_t, uint16_t>(a, ksize, st);
   else if (dtype == APS_BF16 && y_dtype == APS_F32) dispatch_ks<uint16_t, float>(a, ksize, st);
   else return APS_ERR_UNSUPPORTED;
   APS_LAUNCH_CHECK();
   return APS_OK;
+}
+
+int aps_conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,
+                   const void* packed_w, const float* bias, int Cout, int ksize, int relu,
+                   int dtype, void* y, int ldy, int y_dtype, void* stream) {
+  return conv2d_fwd(x, x2, N, H, W, Cx, C2, mode, packed_w, bias, Cout, ksize, relu, dtype, y, ldy,
+                    y_dtype, stream, false);
+}
+
+int aps_conv2d_fwd_train(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,
+                         const void* packed_w, const float* bias, int Cout, int ksize, int relu,
+                         int dtype, void* y, int ldy, int y_dtype, void* stream) {
+  return conv2d_fwd(x, x2, N, H, W, Cx, C2, mode, packed_w, bias, Cout, ksize, relu, dtype, y, ldy,
+                    y_dtype, stream, true);
 }
 
 }  // extern "C"

@@ -328,5 +328,8 @@ __device__ inline void conv_epilogue(const ConvArgs& a, f32x4 (&acc)[TM][TN], in
 // (fp32_offsets_fit).  hw set: with the fused 1x1 head.
 void pack_split(const float* w, int Cout, int Cin, void* packed, int transpose, hipStream_t st);
 void conv_split(const ConvArgs& a, hipStream_t st);
+// the same layers forward in training with a ReLU (conv_f32_train.hip), their own packing
+void pack_f32c16(const float* w, int Cout, int Cin, void* packed, hipStream_t st);
+void conv_f32(const ConvArgs& a, hipStream_t st);
 
 }  // namespace aps

@@ -257,8 +257,9 @@ class Net:
 
 
 def conv2d(x, layer_spec, packed, bias, mode: str = "direct", x2=None, out_dtype=None,
-           ldy: int | None = None, out=None):
-    """One conv layer through aps_conv2d_fwd (mode: direct | pool2 | up2cat)."""
+           ldy: int | None = None, out=None, train: bool = False):
+    """One conv layer through aps_conv2d_fwd (mode: direct | pool2 | up2cat); train: through
+    aps_conv2d_fwd_train, packed by aps_conv_pack_weights_train."""
     _need(x, "x")
     N = x.shape[0]
     if mode == "direct":
@@ -278,9 +279,10 @@ def conv2d(x, layer_spec, packed, bias, mode: str = "direct", x2=None, out_dtype
     ldy = ldy or cout
     if out is None:
         out = torch.empty((N, H, W, ldy), dtype=out_dtype, device=x.device)
-    L.check(L.load().aps_conv2d_fwd(_p(x), _p(x2), N, H, W, Cx, C2, m, _p(packed), _p(bias), cout,
-                                    layer_spec["k"], int(layer_spec["relu"]), _dt(x.dtype), _p(out),
-                                    ldy, _dt(out_dtype), _stream()), "conv2d")
+    lib = L.load()
+    fwd = lib.aps_conv2d_fwd_train if train else lib.aps_conv2d_fwd
+    L.check(fwd(_p(x), _p(x2), N, H, W, Cx, C2, m, _p(packed), _p(bias), cout, layer_spec["k"],
+                int(layer_spec["relu"]), _dt(x.dtype), _p(out), ldy, _dt(out_dtype), _stream()), "conv2d")
     return out
 
 
