@@ -747,8 +747,8 @@ size_t packed_elems(int Cout, int KS, int Cin) {
   const size_t nct = (size_t)((Cout + 16 * kMaxTM - 1) / (16 * kMaxTM)) * kMaxTM;
   const int cg = conv_cg(KS, Cin, Cout);
   if (cg < 4) return nct * ((KS * KS * cg + 3) / 4) * 512;
-  const size_t nchunk = (size_t)(Cin + kChunk - 1) / kChunk;
-  return nct * KS * KS * nchunk * 512;
+  const size_t nchunk = (size_t)(Cin + kChunk - 1) / kChunk, elems = nct * KS * KS * nchunk * 512;
+  return KS == 3 ? std::max(elems, f32_pack(Cout, Cin).total) : elems;
 }
 
 template <typename T, typename TO, int KS, int TM, int TN, int CG>
@@ -1297,7 +1297,6 @@ static int pack_impl(const float* w, int Cout, int ksize, int Cin, int dtype, vo
   const int blocks = (int)((total + 255) / 256);
   hipStream_t st = as_stream(stream);
   if (dtype == APS_F32 && ksize == 3 && conv_cg(3, ci, co) == 4) {
-    // two halves per weight: the same bytes as one float
     pack_split(w, co, ci, packed, transpose, st);
   } else if (dtype == APS_F32)
     k_pack<float><<<blocks, 256, 0, st>>>(w, co, ksize, ci, nchunk, total,

@@ -324,6 +324,18 @@ __device__ inline void conv_epilogue(const ConvArgs& a, f32x4 (&acc)[TM][TN], in
   }
 }
 
+// Packed weights of an fp32 3x3 layer in 32-channel chunks, in floats: the fp16 halves, the weights as
+// they are in 16-channel chunks (k_pack_split's plain part), and a scale exponent per output channel.
+// All three are exact in 16-channel output tiles.
+struct F32Pack {
+  size_t plain, table, total;
+};
+__host__ __device__ inline F32Pack f32_pack(int Cout, int Cin) {
+  const size_t ct = (size_t)(Cout + 15) / 16, split = ct * 9 * ((Cin + 31) / 32) * 512;
+  const size_t plain = ct * 9 * ((Cin + 15) / 16) * 256;
+  return F32Pack{split, split + plain, split + plain + ct * 16};
+}
+
 // fp32 3x3 layers in 32-channel chunks (conv_f32.hip); sizes checked by the entry points
 // (fp32_offsets_fit).  hw set: with the fused 1x1 head.
 void pack_split(const float* w, int Cout, int Cin, void* packed, int transpose, hipStream_t st);

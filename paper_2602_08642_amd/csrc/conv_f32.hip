@@ -2,39 +2,41 @@
 // 9..16 with whole 16-channel output tiles beyond 16) on the fp16 matrix pipe.
 //
 // The fp32 MFMA runs at 1/16 of the fp16 rate, and at 80 % of it the tiled fp32 kernels had nowhere
-// to go.  A float splits into two halves x = h + l with h = fp16(x), l = fp16(x - h), which hold 22
-// to 23 of its 24 bits, and x w = h_x h_w + h_x l_w + l_x h_w up to 2^-22 of the product: three
+// to go.  A float splits into two halves x = h + l with h = fp16(x), l = fp16(x - h), which hold 23 of
+// its 24 bits, and x w = h_x h_w + h_x l_w + l_x h_w up to 2^-22 of the product: three
 // v_mfma_f32_16x16x32_f16 with fp32 accumulation do the work of eight v_mfma_f32_16x16x4_f32, and
 // the sum has a fifth of the roundings.  Range: the operands are scaled by powers of two, which is
-// exact.
-//  * Weights per output channel at packing time, its largest magnitude to [2^14, 2^15); the exponent
-//    travels in the lowest bits of the l halves of the channel's first eight weights.
+// exact, and both l halves carry a factor 2^11, which keeps their bits above the fp16 subnormals: all of
+// an operand's bits are there down to 2^-26 of the largest (kTop, kLow).  The cross products, 2^11 too
+// large, are summed apart and added once per chunk.
+//  * Weights per output channel at packing time, the largest to [2^14, 2^15); the exponents are in a
+//    table behind the weights.  A channel whose weights are further apart than 2^26, or not finite, puts
+//    its block of 32 or 64 channels on plain fp32 products (below).
 //  * Activations per block: before a chunk is staged, its largest finite magnitude over the block's
 //    tile sets the scale (a running maximum over the chunks; the accumulators are rescaled when it
 //    grows), but at most 2^26 times its typical magnitude (the mean exponent of a sample), so that an
 //    outlier does not cost its neighbours their precision: what is larger than the scale allows
-//    overflows and goes the way of infinities, below.  The staged l halves carry a factor 2^11,
-//    undone in the h_w they meet, which keeps them out of the fp16 subnormals: an element is carried
-//    to 2^-23 of itself or 2^-50 of the tile's largest (2^-24 of its typical) element.
-//  * An output that comes out non-finite (an input that is infinite or NaN, an overflow) is summed
-//    again in plain fp32 (rescue), so such values propagate as in an fp32 convolution.
+//    overflows and goes the way of infinities, below: an element is carried to 2^-23 of itself or 2^-50
+//    of the tile's largest (2^-24 of its typical) element.
+//  * A block with an output that comes out non-finite (an input that is infinite or NaN, an overflow) is
+//    summed again in plain fp32 products, from the weights as they are, in the order of k_conv_f32
+//    (equal bits).
 // Error against FP64 (normwise; fp32 MFMA kernels in brackets): 128 -> 128 channels 3.7e-7 (4.3e-7),
 // the U-Net's heads at 1920 x 1080 at most 1.6e-6 (1.7e-6).
 //
 // Tiling as k_conv_lds: blocks of 4 waves stacked vertically, TN rows x 16 px each, all sharing TM
 // m-tiles; the chunk's input tile with its halo in LDS as two planes (64-byte pixels, 16-byte
-// groups swizzled on bits 1-2 of the pixel index).  Taps in order, dx outer: the next tap's B
-// operands are read during the current one's MFMAs.  The weight operands (A) come straight from
-// global memory (the four waves read the same fragments from L1) and each m-tile's are reloaded in
-// place after its last use, 36 MFMAs ahead of the next, so no barrier and no LDS space goes to them.
-// One order of sums for every entry point: 32-channel chunks, taps dx outer and dy inner, the three
-// products, then the bias; the block's tile decides the scale, so launches of equal sizes agree bit
-// for bit.
-// What bounds it: for 32-channel blocks the vector memory path (address unit 80 % busy, mostly with
-// A) and 1000 vector instructions per wave and chunk beside 216 MFMAs; for 64-channel blocks the
-// MFMAs (54 % of the rate at the 2.0 GHz the card holds).  1920 x 1080, before (fp32 MFMA) and now:
-// 16 -> 32 162 -> 181 us, 32 -> 32 317 -> 190 us, 64 -> 64 (540 x 960) 322 -> 120 us, 128 -> 128
-// (270 x 480) 298 -> 103 us, 384 -> 128 841 -> 284 us, 96 -> 32 899 -> 367 us; the U-Net 5.59 -> 2.36 ms.
+// groups swizzled on bits 1-2 of the pixel index).  Two m-tiles at a time go through the taps, dx
+// outer (so that the cross products of two suffice): each B operand is read again in place for the
+// next tap after its last use.  The weight operands (A) come straight from global memory (the four
+// waves read the same fragments from L1), a tap ahead, so no barrier and no LDS space goes to them.
+// One order of sums for every entry point: 32-channel chunks, taps dx outer and dy inner, then the
+// bias; the block's tile decides the scale, so launches of equal sizes agree bit for bit.
+// What bounds it: for 32-channel blocks one chunk's latency (load, scale, staging, MFMAs in turn, with
+// three blocks per CU) and 1000 vector instructions per wave and chunk beside 216 MFMAs; for 64-channel
+// blocks the MFMAs.  1920 x 1080, before (fp32 MFMA) and now:
+// 16 -> 32 162 -> 175 us, 32 -> 32 317 -> 191 us, 64 -> 64 (540 x 960) 322 -> 127 us, 128 -> 128
+// (270 x 480) 298 -> 104 us, 384 -> 128 841 -> 292 us, 96 -> 32 899 -> 360 us; the U-Net 5.59 -> 2.36 ms.
 // Not kept: persistent blocks (fetching the next tile during the current one: registers spill),
 // weights of all three tap rows live at once (spills), 8 channels per staging load.
 #include <algorithm>
@@ -72,66 +74,55 @@ __device__ inline int opaque(int v) {
   return v;
 }
 
-// Exponent that scales a largest magnitude m (0, or finite) to [2^14, 2^15)
-__device__ inline int scale_exp(float m) {
-  const int e = 14 - ((int)((__builtin_bit_cast(uint32_t, m) >> 23) & 0xff) - 127);
-  return m == 0.f ? 0 : e > 126 ? 126 : e;
+// A value of exponent field f scaled by 2^e lies in the halves' range if f + e is at most kTop (h below
+// 2^15) and, for all of its bits, at least kLow (its last place at 2^-35, that of l); subnormals
+// count as f = 1.
+constexpr int kTop = 141, kLow = 115;
+constexpr int kPlain = 0x7fffffff;  // in the exponent table: not a channel for the halves
+__device__ inline int exp_field(float v) { return std::max((int)(__builtin_bit_cast(uint32_t, v) >> 23 & 0xff), 1); }
+
+// A of v_mfma_f32_16x16x4_f32, four steps: channels 4 g + [0, 4) of lane group g
+__device__ inline f32x4 mma4(f32x4 a, f32x4 b, f32x4 c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
 }
 
-// Input channel ci of pixel (iy, ix) after the input transform, in the order of stage8
+// Input channels [ci, ci + 4) of pixel (iy, ix) after the input transform, in the order of stage8 (channel
+// counts are multiples of 4); zeros outside the image and from channel `past` on
 template <int MODE>
-__device__ inline float conv_input(const ConvArgs& a, int n, int iy, int ix, int ci) {
+__device__ inline f32x4 conv_input4(const ConvArgs& a, int n, int iy, int ix, int ci, int past) {
   const float* x = static_cast<const float*>(a.x);
   const float* x2 = static_cast<const float*>(a.x2);
-  if (iy < 0 || iy >= a.H || ix < 0 || ix >= a.W) return 0.f;
+  f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (iy < 0 || iy >= a.H || ix < 0 || ix >= a.W || ci >= past) return v;
+  auto get = [](const float* p) { return *reinterpret_cast<const f32x4*>(p); };
   if constexpr (MODE == APS_CONV_POOL2) {
     const size_t rs = 2 * (size_t)a.W * a.Cx;
     const float* p = x + (((size_t)n * 2 * a.H + 2 * iy) * 2 * a.W + 2 * ix) * a.Cx + ci;
-    return ((p[0] + p[a.Cx]) + (p[rs] + p[rs + a.Cx])) * 0.25f;
+    v = ((get(p) + get(p + a.Cx)) + (get(p + rs) + get(p + rs + a.Cx))) * 0.25f;
   } else if constexpr (MODE == APS_CONV_UP2_CAT) {
-    return ci < a.Cx ? x[(((size_t)n * (a.H / 2) + iy / 2) * (a.W / 2) + ix / 2) * a.Cx + ci]
-                     : x2[(((size_t)n * a.H + iy) * a.W + ix) * a.C2 + (ci - a.Cx)];
+    v = get(ci < a.Cx ? x + (((size_t)n * (a.H / 2) + iy / 2) * (a.W / 2) + ix / 2) * a.Cx + ci
+                      : x2 + (((size_t)n * a.H + iy) * a.W + ix) * a.C2 + (ci - a.Cx));
   } else {
     const size_t o = (((size_t)n * a.H + iy) * a.W + ix) * a.Cx + ci;
-    if constexpr (MODE == kModeReluMask) return x2[o] > 0.f ? x[o] : 0.f;
-    return x[o];
+    v = get(x + o);
+    if constexpr (MODE == kModeReluMask) {
+      const f32x4 y = get(x2 + o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = y[q] > 0.f ? v[q] : 0.f;
+    }
   }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (ci + q >= past) v[q] = 0.f;
+  return v;
 }
 
 // Fragment f (in units of 512 halves) of channel tile ct, tap t, chunk c, half p (0: h, 1: l)
 __device__ inline uint32_t wfrag(int ct, int t, int c, int p, int nchunk) {
   return (uint32_t)(((ct * 9 + t) * nchunk + c) * 2 + p) * 512u;
-}
-
-// Scale exponent of output channel 16 ct + k: e + 128 in the lowest bits of the l halves of weights
-// (tap 0, input channels 0..7), bit exp_bit(b) in channel b
-__device__ inline int exp_bit(int b) { return (b >> 1) + 4 * (b & 1); }
-__device__ inline int weight_exp(const uint16_t* wp, int ct, int k, int nchunk) {
-  const u32x4 v = *reinterpret_cast<const u32x4*>(wp + wfrag(ct, 0, 0, 1, nchunk) + k * 8);
-  const uint32_t t = (v[0] & 0x10001) | (v[1] & 0x10001) << 1 | (v[2] & 0x10001) << 2 | (v[3] & 0x10001) << 3;
-  const int e = (t & 15) | (t >> 12 & 0xf0);
-  return e ? e - 128 : 0;  // no bits: the channel's weights are all zero
-}
-
-// One output channel of one pixel in plain fp32
-template <int MODE>
-__device__ inline float rescue(const ConvArgs& a, const uint16_t* wp, int n, int row, int col, int co) {
-  const int Cin = a.cvalid, ct = co >> 4, k = co & 15;
-  const float sw = pow2(-weight_exp(wp, ct, k, a.nchunk));
-  float s = 0.f;
-  for (int c = 0; c < a.nchunk; ++c)
-    for (int d = 0; d < 9; ++d) {
-      const int t = (d % 3) * 3 + d / 3;  // taps dx outer, dy inner
-      for (int g = 0; g < 4; ++g)
-        for (int e = 0; e < 8; ++e) {
-          const int ci = c * 32 + g * 8 + e;
-          if (ci >= Cin) continue;
-          const uint32_t o = wfrag(ct, t, c, 0, a.nchunk) + (g * 16 + k) * 8 + e;
-          const float w = ((float)__builtin_bit_cast(_Float16, wp[o]) + (float)__builtin_bit_cast(_Float16, wp[o + 512])) * sw;
-          s += w * conv_input<MODE>(a, n, row + t / 3 - 1, col + t % 3 - 1, ci);
-        }
-    }
-  return s;
 }
 
 // The value of lane l ^ 1 (DPP quad_perm [1,0,3,2]).  By value on purpose: a bit cast applied
@@ -183,12 +174,8 @@ __device__ inline void epilogue_f32(const ConvArgs& a, f32x4 (&acc)[TM][TN], int
   }
 }
 
-// PF: the next chunk's loads are in flight during the MFMAs (two blocks per CU).  Without it three
-// 32-channel blocks fit, which is worth more to them (96 -> 32 channels at 1080p: 387 us with, 347 us
-// without; 192 -> 64 at 540 x 960: 284 and 295 us).  A single chunk has no next one (64-channel
-// blocks held to three per CU spill: 32 -> 64 at 540 x 960 97 us against 84 us).
-template <int MODE, int TM, int TN, int HEAD, bool PF>
-__global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a) {
+template <int MODE, int TM, int TN, int HEAD>
+__global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a) {
   constexpr int ROWS = 4 * TN, SH = ROWS + 2, SW = 18, NPX = SH * SW;
   constexpr int NXT = (NPX * 8 + 255) / 256;  // (pixel, 4 channels) items per thread and chunk
   constexpr int PL = NPX * 32;          // halves per plane
@@ -204,7 +191,6 @@ __global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvA
   const int cob = tid_.cob, n = blockIdx.z;
   const float* x = static_cast<const float*>(a.x);
   const float* x2 = static_cast<const float*>(a.x2);
-  const uint16_t* wp = static_cast<const uint16_t*>(a.wp);
   const int Cin = a.Cx + a.C2;
   // This thread stages channels [g4, g4 + 4) of tile pixels tid / 8 + 32 k: a wave's load reads 8
   // pixels' whole 128-byte chunks (with 8 channels per thread and 16 pixels per load the same bytes
@@ -234,7 +220,6 @@ __global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvA
       }
     }
   };
-  offsets(false);
   const size_t row0 = (size_t)n * a.H + yb;
   const float* xb = MODE == APS_CONV_POOL2 ? x + row0 * 4 * a.W * a.Cx
                     : MODE == APS_CONV_UP2_CAT ? x + ((size_t)n * (a.H / 2) + yb / 2) * (a.W / 2) * a.Cx
@@ -245,22 +230,20 @@ __global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvA
   const float* sb = x2 + row0 * a.W * (MODE == APS_CONV_UP2_CAT ? a.C2 : a.Cx);
   const uint32_t sbytes = (uint32_t)rows * a.W * (MODE == APS_CONV_UP2_CAT ? a.C2 : a.Cx) * 4;
 
-  // Global loads of the next chunk, unconditional: no branch join makes the compiler wait for them
-  // before the current chunk's MFMAs (the pooled and masked transforms are evaluated here).
+  // Global loads of a chunk (the pooled and masked transforms are evaluated here).  Not fetched ahead
+  // during the MFMAs: 44 registers that cost the 32-channel blocks one of three blocks per CU and make
+  // the 64-channel blocks spill (64 -> 64 at 540 x 960 127 us, 149 with it), for two blocks overlap.
   f32x4 px[NXT];
   auto fetch = [&](int c) {
     const int cb = c * 32, ch = cb + g4;
-    if (MODE == APS_CONV_UP2_CAT && cb >= a.Cx && cb < a.Cx + 32) offsets(true);  // the first such chunk
-    // element by element: input rows whose bytes do not fit 32-bit offsets, and a chunk that spans
-    // both tensors of the concat
+    if (cb == 0 || (MODE == APS_CONV_UP2_CAT && cb >= a.Cx && cb < a.Cx + 32)) offsets(cb >= a.Cx);
+    // input rows whose bytes do not fit 32-bit offsets, and a chunk that spans both tensors of the concat
     if (a.big || (MODE == APS_CONV_UP2_CAT && cb < a.Cx && cb + 32 > a.Cx)) {
 #pragma unroll
       for (int k = 0; k < NXT; ++k) {
         __builtin_amdgcn_sched_barrier(0);  // one item's addresses live at a time
-        const int p = opaque(pl) + 32 * k, r = p / SW, iy = ty0 - 1 + r, ix = tx0 - 1 + p - r * SW;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          px[k][q] = p < NPX && ch + q < Cin ? conv_input<MODE>(a, n, iy, ix, ch + q) : 0.f;
+        const int p = opaque(pl) + 32 * k, r = p / SW;
+        px[k] = conv_input4<MODE>(a, n, ty0 - 1 + r, tx0 - 1 + p - r * SW, ch, p < NPX ? a.cvalid : 0);
       }
       return;
     }
@@ -289,13 +272,24 @@ __global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvA
   };
 
   const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
-  f16x8 A[TM][2];  // [m-tile][h, l] of the current tap
-  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(wp), 0, 0xffffffffu, 0x00020000);
-  auto load_a = [&](int m, int dy, int dx, int c) {
+  const F32Pack pk = f32_pack(a.Cout, a.cvalid);
+  const float* wf = static_cast<const float*>(a.wp);
+  // the block's scale exponents, channel 16 cob TM + lane; in plain fp32 if one channel has none
+  const int nch = (a.Cout + 15) / 16 * 16, ch0 = cob * TM * 16;
+  const int we = lane < TM * 16 && ch0 + lane < nch ? reinterpret_cast<const int*>(wf + pk.table)[ch0 + lane] : 0;
+  // Tiles past the last output channel read zeros.  Two m-tiles of a tap at a time (load_a: step s is
+  // tap s % 9 of the m-tiles 2 (s / 9) + [0, 2)).
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wf), 0, (uint32_t)(pk.plain * 4), 0x00020000);
+  constexpr int S = TM / 2 * 9;
+  f16x8 A[2][2][2];  // [step parity][m-tile][h, l]
+  auto load_a = [&](int s, int c, f16x8 (&v)[2][2]) {
+    const int t = s % 9, dx = t / 3, dy = t % 3;
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-      A[m][p] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(
-          wr, lane * 16, wfrag(cob * TM + m, dy * 3 + dx, c, p, a.nchunk) * 2, 0));
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        v[q][p] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(
+            wr, lane * 16, wfrag(cob * TM + s / 9 * 2 + q, dy * 3 + dx, c, p, a.nchunk) * 2, 0));
   };
 
   f32x4 acc[TM][TN];
@@ -306,11 +300,10 @@ __global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvA
   int erun = 0;  // largest biased exponent that has set the scale in this block
   int ex = 0;    // the activations' scale exponent
 
-  if (PF) fetch(0);
-#pragma unroll
-  for (int m = 0; m < TM; ++m) load_a(m, 0, 0, 0);
-  for (int c = 0; c < a.nchunk; ++c) {
-    if (!PF) fetch(c);
+  load_a(0, 0, A[0]);
+  bool plain = __any(we == kPlain);
+  for (int c = 0; c < a.nchunk && !plain; ++c) {
+    fetch(c);
     // the chunk's largest finite magnitude over the block (the barrier also ends the previous
     // chunk's reads of Xs)
     if (c * 32 + 32 > a.cvalid) {  // channels past the layer's inputs (padded rows)
@@ -394,76 +387,115 @@ __global__ __launch_bounds__(256, PF || TM == 4 ? 2 : 3) void k_conv_split(ConvA
     }
     __syncthreads();
     const bool more = c + 1 < a.nchunk;
-    if (PF && more) fetch(c + 1);
-    if constexpr (MODE == APS_CONV_POOL2 || MODE == kModeReluMask) __builtin_amdgcn_sched_barrier(0);
-    f16x8 B[2][TN][2];
-    auto load_b = [&](int t, f16x8 (&v)[TN][2]) {
-      const int dx = t / 3, dy = t % 3, col = (lane & 15) + dx;
+    f16x8 B[TN][2];
+    uint32_t bo[4];  // of a tap column: offsets for rows r % 4, recomputed (held over the chunks they spill)
+    auto load_b = [&](int t, int j) {
+      const int dx = t / 3, dy = t % 3;
+      if (dy == 0 && j == 0) {
+        const int l = opaque(lane), col = (l & 15) + dx;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int row = wave * TN + dy + j;  // pixel row SW + col, (pixel >> 1) % 4 = (row + col / 2) % 4
-        const uint16_t* bp = Xs + (row * SW + col) * 32 + (((lane >> 4) ^ ((row + (col >> 1)) & 3)) << 3);
-#pragma unroll
-        for (int p = 0; p < 2; ++p) v[j][p] = *reinterpret_cast<const f16x8*>(bp + p * PL);
+        for (int r = 0; r < 4; ++r)
+          bo[r] = (wave * TN * SW + col) * 32 + (((l >> 4) ^ ((wave * TN + r + (col >> 1)) & 3)) << 3);
       }
+      const uint16_t* bp = Xs + bo[(dy + j) & 3] + (dy + j) * SW * 32;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) B[j][p] = *reinterpret_cast<const f16x8*>(bp + p * PL);
     };
-    load_b(0, B[0]);
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {  // taps dx outer, dy inner
-      __builtin_amdgcn_sched_barrier(0);  // one tap's operands (and the next one's) live at a time
-      if (t < 8) load_b(t + 1, B[(t + 1) & 1]);
-      auto& b = B[t & 1];
+    for (int j = 0; j < TN; ++j) load_b(0, j);
 #pragma unroll
-      for (int m = 0; m < TM; ++m) {
+    for (int g = 0; g < TM / 2; ++g) {
+      f32x4 cr[2][TN];  // the cross products, 2^11 too large
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[m][j] = mmah(A[m][1], b[j][0], acc[m][j]);
-        const f16x8 hs = A[m][0] * (_Float16)0x1p-11f;  // the staged l halves carry 2^11
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[m][j] = mmah(hs, b[j][1], acc[m][j]);
+        for (int j = 0; j < TN; ++j) cr[q][j] = zero4;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[m][j] = mmah(A[m][0], b[j][0], acc[m][j]);
-        // the m-tile's operands for the next tap
-        if (t < 8) load_a(m, (t + 1) % 3, (t + 1) / 3, c);
-        else if (more) load_a(m, 0, 0, c + 1);
+      for (int t = 0; t < 9; ++t) {  // taps dx outer, dy inner
+        const int s = g * 9 + t;
+        __builtin_amdgcn_sched_barrier(0);  // one step's operands (and the next one's weights) live at a time
+        if (s + 1 < S) load_a(s + 1, c, A[(s + 1) & 1]);
+        const auto& w = A[s & 1];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) cr[q][j] = mmah(w[q][1], B[j][0], cr[q][j]);
+#pragma unroll
+          for (int q = 0; q < 2; ++q) acc[2 * g + q][j] = mmah(w[q][0], B[j][0], acc[2 * g + q][j]);
+#pragma unroll
+          for (int q = 0; q < 2; ++q) cr[q][j] = mmah(w[q][0], B[j][1], cr[q][j]);
+          if (s + 1 < S) load_b((s + 1) % 9, j);  // in place
+        }
       }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[2 * g + q][j] += cr[q][j] * 0x1p-11f;
     }
+    if (more) load_a(0, c + 1, A[0]);
   }
 
-  // back to the layer's scale (exact), the bias, and plain fp32 where a sum is not finite
-  float nf = 0.f;  // NaN if any sum is not finite
+  if (!plain) {
+    // back to the layer's scale (exact) and the bias; in plain fp32 if a sum of the block is not finite
+    float nf = 0.f;  // NaN if any sum is not finite
 #pragma unroll
-  for (int m = 0; m < TM; ++m) {
-    const int ct = cob * TM + m, co0 = ct * 16 + 4 * (lane >> 4);
-    if (ct * 16 >= a.Cout) continue;
-    int se[4];
-    float bv[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      se[q] = -ex - weight_exp(wp, ct, 4 * (lane >> 4) + q, a.nchunk);
-      bv[q] = a.bias && co0 + q < a.Cout ? a.bias[co0 + q] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int m = 0; m < TM; ++m) {
+      const int co0 = (cob * TM + m) * 16 + 4 * (lane >> 4);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        nf = __builtin_fmaf(acc[m][j][q], 0.f, nf);
-        acc[m][j][q] = __builtin_ldexpf(acc[m][j][q], se[q]) + bv[q];
+        const int se = -ex - __shfl(we, m * 16 + 4 * (lane >> 4) + q, 64);
+        const float bv = a.bias && co0 + q < a.Cout ? a.bias[co0 + q] : 0.f;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          nf = __builtin_fmaf(acc[m][j][q], 0.f, nf);
+          acc[m][j][q] = __builtin_ldexpf(acc[m][j][q], se) + bv;
+        }
       }
+    }
+    plain = __syncthreads_or(nf != 0.f);
   }
-  if (__any(nf != 0.f)) {
-    const int col = tx0 + (lane & 15);
-    for (int i = 0; i < TM * TN * 4; ++i) {  // one copy of the loop, the accumulator by selection
-      const int m = i / (TN * 4), j = (i / 4) % TN, q = i & 3;
-      const int row = ty0 + wave * TN + j, co = (cob * TM + m) * 16 + 4 * (lane >> 4) + q;
-      float v = 0.f;
+  if (plain) {
+    // k_conv_f32's sums: the bias, 16-channel chunks, taps dx outer and dy inner, plain fp32 products
+    const int tid = opaque(threadIdx.x), lane = tid & 63, pl = tid >> 3, g4 = (tid & 7) * 4;
+    float* Xf = reinterpret_cast<float*>(Xs);  // 32 channels a pixel, their 16-byte groups permuted
+    const __amdgpu_buffer_rsrc_t pr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wf) + pk.plain, 0, (uint32_t)((pk.table - pk.plain) * 4), 0x00020000);
+    const int n16 = (a.cvalid + 15) / 16;
 #pragma unroll
-      for (int k = 0; k < TM * TN * 4; ++k)
-        if (k == i) v = acc[k / (TN * 4)][(k / 4) % TN][k & 3];
-      if (__builtin_fabsf(v) < __builtin_inff() || row >= a.H || col >= a.W || co >= a.Cout) continue;
-      v = rescue<MODE>(a, wp, n, row, col, co) + (a.bias ? a.bias[co] : 0.f);
+    for (int m = 0; m < TM; ++m) {
+      const int co0 = (cob * TM + m) * 16 + 4 * (lane >> 4);
+      f32x4 b0 = zero4;
 #pragma unroll
-      for (int k = 0; k < TM * TN * 4; ++k)
-        if (k == i) acc[k / (TN * 4)][(k / 4) % TN][k & 3] = v;
+      for (int q = 0; q < 4; ++q)
+        if (a.bias && co0 + q < a.Cout) b0[q] = a.bias[co0 + q];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[m][j] = b0;
+    }
+    for (int c = 0; c < a.nchunk; ++c) {
+      __syncthreads();
+#pragma unroll 1
+      for (int p = pl; p < NPX; p += 32) {
+        const int r = p / SW;
+        *reinterpret_cast<f32x4*>(Xf + p * 32 + (((g4 >> 2) ^ (p & 7)) << 2)) =
+            conv_input4<MODE>(a, n, ty0 - 1 + r, tx0 - 1 + p - r * SW, c * 32 + g4, a.cvalid);
+      }
+      __syncthreads();
+      for (int c16 = 2 * c; c16 < std::min(2 * c + 2, n16); ++c16)
+#pragma unroll 1
+        for (int t = 0; t < 9; ++t) {
+          const int dx = t / 3, dy = t % 3;
+          f32x4 W[TM];
+#pragma unroll
+          for (int m = 0; m < TM; ++m)
+            W[m] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                pr, lane * 16, (uint32_t)((((cob * TM + m) * 9 + dy * 3 + dx) * n16 + c16) * 1024), 0));
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const int p = (wave * TN + dy + j) * SW + (lane & 15) + dx;
+            const f32x4 b = *reinterpret_cast<const f32x4*>(Xf + p * 32 + ((((c16 & 1) * 4 + (lane >> 4)) ^ (p & 7)) << 2));
+#pragma unroll
+            for (int m = 0; m < TM; ++m) acc[m][j] = mma4(W[m], b, acc[m][j]);
+          }
+        }
     }
   }
   if constexpr (HEAD) {
@@ -489,52 +521,62 @@ void launch_m(const ConvArgs& a, hipStream_t st) {
   b.ntiles = b.ntx * ((a.H + rows - 1) / rows);
   b.nco = wide ? (a.Cout + 63) / 64 : 1;
   dim3 grid(xcd_grid(b.ntiles, b.nco), 1, a.N);
-  const bool pf = b.nchunk > 1;
   if (!wide) {
-    if (tn2) k_conv_split<MODE, 2, 2, HEAD, false><<<grid, 256, 0, st>>>(b);
-    else k_conv_split<MODE, 2, 4, HEAD, false><<<grid, 256, 0, st>>>(b);
-  } else if (tn2) {
-    if (pf) k_conv_split<MODE, 4, 2, HEAD, true><<<grid, 256, 0, st>>>(b);
-    else k_conv_split<MODE, 4, 2, HEAD, false><<<grid, 256, 0, st>>>(b);
+    if (tn2) k_conv_split<MODE, 2, 2, HEAD><<<grid, 256, 0, st>>>(b);
+    else k_conv_split<MODE, 2, 4, HEAD><<<grid, 256, 0, st>>>(b);
   } else {
-    if (pf) k_conv_split<MODE, 4, 4, HEAD, true><<<grid, 256, 0, st>>>(b);
-    else k_conv_split<MODE, 4, 4, HEAD, false><<<grid, 256, 0, st>>>(b);
+    if (tn2) k_conv_split<MODE, 4, 2, HEAD><<<grid, 256, 0, st>>>(b);
+    else k_conv_split<MODE, 4, 4, HEAD><<<grid, 256, 0, st>>>(b);
   }
 }
 
-// Packing: one block per output channel of the padded channel tiles (the layout of wfrag).
+// Packing: one block per output channel of the 16-channel tiles (the layouts of wfrag and f32_pack).
+// The plain part: [channel tile][tap][16-channel chunk][lane][4], lane l output channel l % 16 and
+// input channels 4 (l / 16) + [0, 4).
 __global__ __launch_bounds__(256) void k_pack_split(const float* __restrict__ w, int Cout, int Cin, int nchunk,
-                                                   uint16_t* __restrict__ out, int transpose) {
-  __shared__ float red[4];
+                                                   float* __restrict__ packed, int transpose) {
+  __shared__ float red[2][4];
   const int co = blockIdx.x, lane = threadIdx.x, ct = co >> 4, k = co & 15;
   auto get = [&](int t, int ci) {
     if (co >= Cout || ci >= Cin) return 0.f;
     return transpose ? w[((size_t)ci * 9 + (8 - t)) * Cout + co] : w[((size_t)co * 9 + t) * Cin + ci];
   };
   const int total = 9 * nchunk * 32;
-  float mx = 0.f;
+  const float inf = __builtin_inff();
+  // the largest and the smallest magnitude that is not zero; the largest infinite if one is not finite
+  float mx = 0.f, mn = inf;
   for (int i = lane; i < total; i += 256) {
     const float v = __builtin_fabsf(get(i / (nchunk * 32), i % (nchunk * 32)));
-    mx = v < __builtin_inff() && v > mx ? v : mx;
+    mx = fmaxf(mx, v < inf ? v : inf);
+    mn = fminf(mn, v == 0.f ? inf : v);
   }
   mx = wave_max(mx);
-  if ((lane & 63) == 0) red[lane >> 6] = mx;
+  mn = -wave_max(-mn);
+  if ((lane & 63) == 0) {
+    red[0][lane >> 6] = mx;
+    red[1][lane >> 6] = mn;
+  }
   __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  const int e = scale_exp(mx), bits = mx == 0.f ? 0 : e + 128;
-  const float s = pow2(e);
+  mx = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+  mn = fminf(fminf(red[1][0], red[1][1]), fminf(red[1][2], red[1][3]));
+  int e = 0;
+  if (mx > 0.f) e = std::min(kTop - exp_field(mx), 126);
+  const bool plain = mx == inf || (mx > 0.f && exp_field(mn) + e < kLow);
+  const float s = plain ? 0.f : pow2(e);
+  const F32Pack pk = f32_pack(Cout, Cin);
+  const int n16 = (Cin + 15) / 16;
+  uint16_t* out = reinterpret_cast<uint16_t*>(packed);
   for (int i = lane; i < total; i += 256) {
     const int t = i / (nchunk * 32), ci = i % (nchunk * 32);
-    const float v = get(t, ci) * s;
-    const _Float16 h = (_Float16)v;
-    // infinities and NaN stay in h alone
-    const _Float16 l = __builtin_fabsf(v) < __builtin_inff() ? (_Float16)(v - (float)h) : (_Float16)0.f;
-    uint16_t lb = __builtin_bit_cast(uint16_t, l);
-    if (t == 0 && ci < 8) lb = (uint16_t)((lb & ~1u) | ((bits >> exp_bit(ci)) & 1));
+    const float x = get(t, ci), v = plain ? 0.f : x * s;
+    const _Float16 h = (_Float16)v, l = (_Float16)((v - (float)h) * 2048.f);
     const uint32_t o = wfrag(ct, t, ci >> 5, 0, nchunk) + ((ci >> 3 & 3) * 16 + k) * 8 + (ci & 7);
     out[o] = __builtin_bit_cast(uint16_t, h);
-    out[o + 512] = lb;
+    out[o + 512] = __builtin_bit_cast(uint16_t, l);
+    if (ci < 16 * n16)
+      packed[pk.plain + ((size_t)(ct * 9 + t) * n16 + (ci >> 4)) * 256 + ((ci >> 2 & 3) * 16 + k) * 4 + (ci & 3)] = x;
   }
+  if (lane == 0) reinterpret_cast<int*>(packed + pk.table)[co] = plain ? kPlain : e;
 }
 
 }  // namespace
@@ -542,8 +584,7 @@ __global__ __launch_bounds__(256) void k_pack_split(const float* __restrict__ w,
 namespace aps {
 
 void pack_split(const float* w, int Cout, int Cin, void* packed, int transpose, hipStream_t st) {
-  const int tiles = (Cout + 16 * kMaxTM - 1) / (16 * kMaxTM) * kMaxTM;
-  k_pack_split<<<tiles * 16, 256, 0, st>>>(w, Cout, Cin, (Cin + 31) / 32, static_cast<uint16_t*>(packed), transpose);
+  k_pack_split<<<(Cout + 15) / 16 * 16, 256, 0, st>>>(w, Cout, Cin, (Cin + 31) / 32, static_cast<float*>(packed), transpose);
 }
 
 void conv_split(const ConvArgs& a, hipStream_t st) {
