@@ -101,10 +101,11 @@ int aps_conv_pack_weights(const float* w, int Cout, int ksize, int Cin, int dtyp
  * shape selects (bf16: the bias, then 32-channel input chunks, taps dx outer and dy inner; fp32: the
  * same without the bias, three products of fp16 halves per tap, then the bias), so this call, the
  * main output of aps_conv2d_fwd_head(_ex) and y of aps_conv2d_fwd_pool agree bit for bit on equal
- * sizes.  fp32: a weight is carried to 2^-23 of itself, an element to 2^-23 of itself or 2^-50 of the
- * largest element of its block's tile (16 columns x 8 or 16 rows and their halo), whichever is larger;
- * non-finite sums, and blocks of 32 (Cout <= 32) or 64 output channels in which the weights of a
- * channel are more than 2^26 apart or not finite, are taken in plain fp32. */
+ * sizes.  fp32: inputs and weights are carried to 2^-23 of themselves.  Where the elements of a chunk in
+ * a block's tile (16 columns x 8 or 16 rows and their halo) are more than 2^26 apart, it is taken in
+ * several passes; where an input or weight is not finite, the weights of an output channel are more
+ * than 2^26 apart or the inputs more than 2^72, a block (of 32 output channels for Cout <= 32, else 64)
+ * is taken in plain fp32 products.  Elsewhere the bits do not depend on N, H or W. */
 int aps_conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,
                    const void* packed_w, const float* bias, int Cout, int ksize, int relu,
                    int dtype, void* y, int ldy, int y_dtype, void* stream);

@@ -12,15 +12,17 @@
 //  * Weights per output channel at packing time, the largest to [2^14, 2^15); the exponents are in a
 //    table behind the weights.  A channel whose weights are further apart than 2^26, or not finite, puts
 //    its block of 32 or 64 channels on plain fp32 products (below).
-//  * Activations per block: before a chunk is staged, its largest finite magnitude over the block's
-//    tile sets the scale (a running maximum over the chunks; the accumulators are rescaled when it
-//    grows), but at most 2^26 times its typical magnitude (the mean exponent of a sample), so that an
-//    outlier does not cost its neighbours their precision: what is larger than the scale allows
-//    overflows and goes the way of infinities, below: an element is carried to 2^-23 of itself or 2^-50
-//    of the tile's largest (2^-24 of its typical) element.
-//  * A block with an output that comes out non-finite (an input that is infinite or NaN, an overflow) is
-//    summed again in plain fp32 products, from the weights as they are, in the order of k_conv_f32
-//    (equal bits).
+//  * Activations per block: before a chunk is staged, the largest and the smallest magnitude of the
+//    block's tile set the scale (kept from chunk to chunk where it holds both; the accumulators are
+//    rescaled where it changes).  A tile that is further apart than 2^26 takes several passes over the
+//    chunk, each with the elements of its range and zeros for the others, so every element is carried to
+//    2^-23 of itself whatever its neighbours are.  An infinity, or scales further apart than 2^72 (kSpan),
+//    put the block on plain fp32 products; NaN needs nothing.
+//  * Plain products: the weights as they are, in the order of k_conv_f32 (equal bits).
+// Time by the input (32 -> 32 at 1920 x 1080, 128 -> 128 at 480 x 270): ordinary tiles 179 and 102 us;
+// half of the elements at 2^-30 or 2^-60 of the others, two passes, 290 and 182; plain products in every
+// block 450 and 340.  (A scale for the typical element, with the outputs that meet a larger one summed
+// again one by one, took 37 and 36 ms for half of the elements 2^30 apart.)
 // Error against FP64 (normwise; fp32 MFMA kernels in brackets): 128 -> 128 channels 3.7e-7 (4.3e-7),
 // the U-Net's heads at 1920 x 1080 at most 1.6e-6 (1.7e-6).
 //
@@ -30,8 +32,9 @@
 // outer (so that the cross products of two suffice): each B operand is read again in place for the
 // next tap after its last use.  The weight operands (A) come straight from global memory (the four
 // waves read the same fragments from L1), a tap ahead, so no barrier and no LDS space goes to them.
-// One order of sums for every entry point: 32-channel chunks, taps dx outer and dy inner, then the
-// bias; the block's tile decides the scale, so launches of equal sizes agree bit for bit.
+// One order of sums for every entry point and size: 32-channel chunks, taps dx outer and dy inner, then
+// the bias.  Powers of two change no bits, so the tile an output lies in matters only where it takes
+// several passes over a chunk or plain products.
 // What bounds it: for 32-channel blocks one chunk's latency (load, scale, staging, MFMAs in turn, with
 // three blocks per CU) and 1000 vector instructions per wave and chunk beside 216 MFMAs; for 64-channel
 // blocks the MFMAs.  1920 x 1080, before (fp32 MFMA) and now:
@@ -51,7 +54,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kOutlier = 26;
 constexpr uint32_t kOut = 0xffffff00u;  // a byte offset past the end of any row_load range
 
 // 16 bytes at byte offset off of a range (uniform base), `skip` floats further on; zeros past its end
@@ -78,6 +80,9 @@ __device__ inline int opaque(int v) {
 // 2^15) and, for all of its bits, at least kLow (its last place at 2^-35, that of l); subnormals
 // count as f = 1.
 constexpr int kTop = 141, kLow = 115;
+// Scales of a block this far apart: the accumulators (sums up to 2^44 at the least scale, last places
+// from 2^-47 at the greatest) stay finite and above the fp32 subnormals when they change scale.
+constexpr int kSpan = 72;
 constexpr int kPlain = 0x7fffffff;  // in the exponent table: not a channel for the halves
 __device__ inline int exp_field(float v) { return std::max((int)(__builtin_bit_cast(uint32_t, v) >> 23 & 0xff), 1); }
 
@@ -181,8 +186,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
   constexpr int PL = NPX * 32;          // halves per plane
   constexpr int XS_HEAD = HEAD ? 2 * head_lds_elems<float, float, TM, HEAD>() : 0;
   __shared__ __attribute__((aligned(16))) uint16_t Xs[2 * PL > XS_HEAD ? 2 * PL : XS_HEAD];
-  __shared__ float red[4];
-  __shared__ uint32_t rede[4];
+  __shared__ float red[2][4];
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const TileId tid_ = xcd_tile(blockIdx.x, a.ntiles, a.nco);
@@ -297,15 +301,13 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
   for (int m = 0; m < TM; ++m)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[m][j] = zero4;
-  int erun = 0;  // largest biased exponent that has set the scale in this block
-  int ex = 0;    // the activations' scale exponent
+  int ex = 0, exlo = 1000, exhi = -1000;  // the activations' scale exponent, the least and greatest so far
+  float lim = 0.f;  // not 0: only the chunk's elements below it are left to do
 
   load_a(0, 0, A[0]);
   bool plain = __any(we == kPlain);
-  for (int c = 0; c < a.nchunk && !plain; ++c) {
+  for (int c = 0; c < a.nchunk && !plain;) {
     fetch(c);
-    // the chunk's largest finite magnitude over the block (the barrier also ends the previous
-    // chunk's reads of Xs)
     if (c * 32 + 32 > a.cvalid) {  // channels past the layer's inputs (padded rows)
 #pragma unroll
       for (int k = 0; k < NXT; ++k)
@@ -313,55 +315,68 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
         for (int q = 0; q < 4; ++q)
           if (c * 32 + g4 + q >= a.cvalid) px[k][q] = 0.f;
     }
-    float mx = 0.f;
-#pragma unroll
-    for (int k = 0; k < NXT; ++k)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) mx = fmaxf(mx, __builtin_fabsf(px[k][q]));
-    if (__any(mx == __builtin_inff())) {  // an infinite input: the scale follows the finite ones
-      mx = 0.f;
+    if (lim != 0.f) {
 #pragma unroll
       for (int k = 0; k < NXT; ++k)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float v = __builtin_fabsf(px[k][q]);
-          mx = v < __builtin_inff() && v > mx ? v : mx;
-        }
+        for (int q = 0; q < 4; ++q) px[k][q] = __builtin_fabsf(px[k][q]) < lim ? px[k][q] : 0.f;
     }
-    // mean exponent of a sample of the finite non-zero elements: sum and count in one word
-    uint32_t es = 0;
+    // the largest and the smallest non-zero magnitude over the block (NaN: in neither; the barrier
+    // also ends the previous chunk's reads of Xs)
+    float mx = 0.f;
+    uint32_t mw = ~0u;  // twice the smallest's bits, less 1: zeros come out largest
 #pragma unroll
-    for (int k = 0; k < NXT; k += 4) {
-      const uint32_t e = __builtin_bit_cast(uint32_t, px[k][k >> 2 & 3]) >> 23 & 0xff;
-      es += e != 0 && e != 255 ? e + 0x10000u : 0u;
-    }
+    for (int k = 0; k < NXT; ++k)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = px[k][q];  // by value: see lane_xor1
+        mx = fmaxf(mx, __builtin_fabsf(v));
+        mw = std::min(mw, (__builtin_bit_cast(uint32_t, v) << 1) - 1);
+      }
+    float mn = mw == ~0u ? __builtin_inff() : __builtin_bit_cast(float, (mw + 1) >> 1);
     mx = wave_max(mx);
-    es = (uint32_t)wave_isum((int)es);
+    mn = wave_max(-mn);
     if (lane == 0) {
-      red[wave] = mx;
-      rede[wave] = es;
+      red[0][wave] = mx;
+      red[1][wave] = mn;
     }
     __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    const int em = __builtin_amdgcn_readfirstlane((int)(__builtin_bit_cast(uint32_t, mx) >> 23 & 0xff));
-    const uint32_t s01 = rede[0], s23 = rede[1], s45 = rede[2], s67 = rede[3];
-    const uint32_t cnt = __builtin_amdgcn_readfirstlane((s01 >> 16) + (s23 >> 16) + (s45 >> 16) + (s67 >> 16));
-    const uint32_t sum = __builtin_amdgcn_readfirstlane((s01 & 0xffff) + (s23 & 0xffff) + (s45 & 0xffff) + (s67 & 0xffff));
-    // an element over 2^kOutlier of the typical one does not set the scale: it overflows, and the
-    // outputs it reaches are summed in fp32
-    const int ec = cnt ? std::min(em, (int)(sum / cnt) + kOutlier) : em;
-    if (em != 0 && ec > erun) {
-      const int en = std::min(14 + 127 - ec, 126);
-      if (erun > 0 && en != ex) {
-        const float f = pow2(std::max(en - ex, -126));
+    auto most = [&](int i) { return fmaxf(fmaxf(red[i][0], red[i][1]), fmaxf(red[i][2], red[i][3])); };
+    auto uniform = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
+    mx = uniform(most(0));
+    mn = -uniform(most(1));
+    bool part = false;  // elements remain for another pass over the chunk
+    if (mx > 0.f) {
+      const int fh = exp_field(mx), fl = exp_field(mn);
+      if (exhi < exlo || fh + ex > kTop || fl + ex < kLow) {
+        // in the middle of what holds them all, so that few chunks move it; else for the largest
+        const int hi = kTop - fh, lo = kLow - fl, en = std::min(lo <= hi ? (lo + hi) >> 1 : hi, 126), d = en - ex;
+        const bool fresh = exhi < exlo;
+        exlo = std::min(exlo, en);
+        exhi = std::max(exhi, en);
+        if (fh == 255 || exhi - exlo > kSpan) {
+          plain = true;
+          break;
+        }
+        ex = en;
+        if (!fresh && d != 0) {
+          const float f = pow2(d);
 #pragma unroll
-        for (int m = 0; m < TM; ++m)
+          for (int m = 0; m < TM; ++m)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[m][j] *= f;
+            for (int j = 0; j < TN; ++j) acc[m][j] *= f;
+        }
       }
-      erun = ec;
-      ex = en;
+      part = fl + ex < kLow;
     }
+    lim = part ? pow2(kLow - 127 - ex) : 0.f;
+    if (part) {
+#pragma unroll
+      for (int k = 0; k < NXT; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) px[k][q] = __builtin_fabsf(px[k][q]) < lim ? 0.f : px[k][q];
+    }
+    const int cn = part ? c : c + 1;
     const float sx = pow2(ex);
 #pragma unroll
     for (int k = 0; k < NXT; ++k) {
@@ -386,7 +401,6 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
       }
     }
     __syncthreads();
-    const bool more = c + 1 < a.nchunk;
     f16x8 B[TN][2];
     uint32_t bo[4];  // of a tap column: offsets for rows r % 4, recomputed (held over the chunks they spill)
     auto load_b = [&](int t, int j) {
@@ -432,12 +446,12 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[2 * g + q][j] += cr[q][j] * 0x1p-11f;
     }
-    if (more) load_a(0, c + 1, A[0]);
+    c = cn;
+    if (c < a.nchunk) load_a(0, c, A[0]);
   }
 
   if (!plain) {
-    // back to the layer's scale (exact) and the bias; in plain fp32 if a sum of the block is not finite
-    float nf = 0.f;  // NaN if any sum is not finite
+    // back to the layer's scale (exact) and the bias
 #pragma unroll
     for (int m = 0; m < TM; ++m) {
       const int co0 = (cob * TM + m) * 16 + 4 * (lane >> 4);
@@ -446,15 +460,10 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
         const int se = -ex - __shfl(we, m * 16 + 4 * (lane >> 4) + q, 64);
         const float bv = a.bias && co0 + q < a.Cout ? a.bias[co0 + q] : 0.f;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          nf = __builtin_fmaf(acc[m][j][q], 0.f, nf);
-          acc[m][j][q] = __builtin_ldexpf(acc[m][j][q], se) + bv;
-        }
+        for (int j = 0; j < TN; ++j) acc[m][j][q] = __builtin_ldexpf(acc[m][j][q], se) + bv;
       }
     }
-    plain = __syncthreads_or(nf != 0.f);
-  }
-  if (plain) {
+  } else {
     // k_conv_f32's sums: the bias, 16-channel chunks, taps dx outer and dy inner, plain fp32 products
     const int tid = opaque(threadIdx.x), lane = tid & 63, pl = tid >> 3, g4 = (tid & 7) * 4;
     float* Xf = reinterpret_cast<float*>(Xs);  // 32 channels a pixel, their 16-byte groups permuted
