@@ -38,14 +38,8 @@ class LayerRef:
         ops.L.check(lib.aps_conv_pack_weights(ops._p(self.w.detach()), self.spec["cout"], self.spec["k"],
                                               self.spec["cin"], ops._dt(self.dtype), ops._p(self.packed),
                                               ops._stream()), "pack_weights")
-        # fp32 layers with a ReLU: the forward pass whose signs the backward pass uses has its own packing
-        self.packed_train = None
-        if self.dtype == F32 and self.spec["k"] == 3 and self.spec["relu"]:
-            self.packed_train = torch.empty_like(self.packed)
-            ops.L.check(lib.aps_conv_pack_weights_train(ops._p(self.w.detach()), self.spec["cout"], self.spec["k"],
-                                                        self.spec["cin"], ops._dt(self.dtype),
-                                                        ops._p(self.packed_train), ops._stream()),
-                        "pack_weights_train")
+        # fp32 layers with a ReLU: the forward pass whose signs the backward pass uses, from the same packing
+        self.packed_train = self.packed if self.dtype == F32 and self.spec["k"] == 3 and self.spec["relu"] else None
         self.packed_T = ops.pack_dgrad(self.spec, self.w.detach(), self.dtype)
 
 

@@ -1318,12 +1318,7 @@ int aps_conv_pack_weights(const float* w, int Cout, int ksize, int Cin, int dtyp
 
 int aps_conv_pack_weights_train(const float* w, int Cout, int ksize, int Cin, int dtype, void* packed,
                                 void* stream) {
-  if (dtype != APS_F32 || ksize != 3 || Cout <= 0 || Cin <= 0 || conv_cg(3, Cin, Cout) != 4)
-    return pack_impl(w, Cout, ksize, Cin, dtype, packed, stream, 0);
-  if (!w || !packed) return APS_ERR_NULL;
-  pack_f32c16(w, Cout, Cin, packed, as_stream(stream));
-  APS_LAUNCH_CHECK();
-  return APS_OK;
+  return pack_impl(w, Cout, ksize, Cin, dtype, packed, stream, 0);  // it holds what both passes read
 }
 
 int aps_conv_pack_weights_dgrad(const float* w, int Cout, int ksize, int Cin, int dtype,

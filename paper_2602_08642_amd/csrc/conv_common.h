@@ -324,6 +324,14 @@ __device__ inline void conv_epilogue(const ConvArgs& a, f32x4 (&acc)[TM][TN], in
   }
 }
 
+// v_mfma_f32_16x16x4_f32, four steps: channels 4 g + [0, 4) of lane group g
+__device__ inline f32x4 mma4(f32x4 a, f32x4 b, f32x4 c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
+}
+
 // Packed weights of an fp32 3x3 layer in 32-channel chunks, in floats: the fp16 halves, the weights as
 // they are in 16-channel chunks (k_pack_split's plain part), and a scale exponent per output channel.
 // All three are exact in 16-channel output tiles.
@@ -340,8 +348,7 @@ __host__ __device__ inline F32Pack f32_pack(int Cout, int Cin) {
 // (fp32_offsets_fit).  hw set: with the fused 1x1 head.
 void pack_split(const float* w, int Cout, int Cin, void* packed, int transpose, hipStream_t st);
 void conv_split(const ConvArgs& a, hipStream_t st);
-// the same layers forward in training with a ReLU (conv_f32_train.hip), their own packing
-void pack_f32c16(const float* w, int Cout, int Cin, void* packed, hipStream_t st);
+// the same layers forward in training with a ReLU (conv_f32_train.hip)
 void conv_f32(const ConvArgs& a, hipStream_t st);
 
 }  // namespace aps

@@ -86,14 +86,6 @@ constexpr int kSpan = 72;
 constexpr int kPlain = 0x7fffffff;  // in the exponent table: not a channel for the halves
 __device__ inline int exp_field(float v) { return std::max((int)(__builtin_bit_cast(uint32_t, v) >> 23 & 0xff), 1); }
 
-// A of v_mfma_f32_16x16x4_f32, four steps: channels 4 g + [0, 4) of lane group g
-__device__ inline f32x4 mma4(f32x4 a, f32x4 b, f32x4 c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
-}
-
 // Input channels [ci, ci + 4) of pixel (iy, ix) after the input transform, in the order of stage8 (channel
 // counts are multiples of 4); zeros outside the image and from channel `past` on
 template <int MODE>

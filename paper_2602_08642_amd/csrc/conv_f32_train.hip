@@ -3,7 +3,10 @@
 // either sign: a forward pass summed in another order or precision (k_conv_split) gives gradients
 // further from these by far more than either one's rounding (128 -> 256 channels at 260 x 278: 5e-4
 // of their norm).  So the training forward pass keeps plain fp32 products in one order (bias, 16-channel
-// chunks, dx outer, dy inner); everything else fp32 runs in k_conv_split, at about 2.5 times the rate.
+// chunks, dx outer, dy inner).  The other passes of the fp32 3x3 layers in 32-channel chunks (inference,
+// data gradients, training layers without a ReLU) run in k_conv_split, at about 2.5 times the rate.
+#include <algorithm>
+
 #include "conv_common.h"
 
 using namespace aps;
@@ -11,13 +14,6 @@ using namespace aps;
 namespace {
 
 constexpr uint32_t kNoPixel = 0xffffffffu;
-
-__device__ inline f32x4 mma4(f32x4 a, f32x4 b, f32x4 c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
-}
 
 // Tile, row reuse and register prefetch of k_conv_lds: chunks of 16 input channels (4 per lane and
 // fragment, 4 MFMAs per fragment pair), pixel stride 20 floats in LDS (conflict-free for the 16 lanes
@@ -30,7 +26,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(ConvArgs a) {
   __shared__ __attribute__((aligned(16))) float Xs[SH * SW * PS];
   __shared__ __attribute__((aligned(16))) float As[NAV * 4];
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const TileId tid_ = xcd_tile(blockIdx.x, a.ntiles, a.nco);
   if (tid_.tile >= a.ntiles) return;
   const int tx0 = (tid_.tile % a.ntx) * 16, ty0 = (tid_.tile / a.ntx) * ROWS;
@@ -63,8 +59,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(ConvArgs a) {
     if constexpr (MODE == APS_CONV_UP2_CAT)
       so[k] = in ? (uint32_t)((((size_t)n * a.H + iy) * a.W + ix) * a.C2 + g4) : kNoPixel;
   }
-  const uint32_t wo = (uint32_t)((((size_t)cob * TM * 9 + wave) * a.nchunk) * 256 + lane * 4);
-  const uint32_t wstep = (uint32_t)(4 * a.nchunk * 256);
+  const int wlast = (a.Cout + 15) / 16 * 9 - 1;  // weight rows (channel tile, tap) past it repeat it
 
   f32x4 px[NXT], pa[NAT];  // clang vector types: HIP's struct vectors are not promoted here
   uint32_t okbits = 0;
@@ -98,7 +93,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(ConvArgs a) {
     }
 #pragma unroll
     for (int k = 0; k < NAT; ++k)
-      pa[k] = *reinterpret_cast<const f32x4*>(wp + ((tid + 256 * k < NAV ? wo + k * wstep : wo) + c * 256));
+      pa[k] = *reinterpret_cast<const f32x4*>(wp + (size_t)(std::min(cob * TM * 9 + wave + 4 * k, wlast) * a.nchunk + c) * 256 + lane * 4);
   };
   auto put = [&]() {
 #pragma unroll
@@ -175,29 +170,12 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(ConvArgs a) {
   }
 }
 
-// packed[(((ct * 9 + tap) * nchunk16 + c) * 64 + lane) * 4 + e] =
-//     w[co = 16 ct + lane % 16][tap][ci = 16 c + 4 (lane / 16) + e]   (0 outside)
-__global__ void k_pack_f32c16(const float* __restrict__ w, int Cout, int Cin, int nchunk16,
-                              size_t total, float* __restrict__ out) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int e = (int)(i & 3), lane = (int)((i >> 2) & 63);
-  size_t r = i >> 8;
-  const int c = (int)(r % nchunk16);
-  r /= nchunk16;
-  const int tap = (int)(r % 9), ct = (int)(r / 9);
-  const int co = ct * 16 + (lane & 15), ci = c * 16 + (lane >> 4) * 4 + e;
-  float v = 0.f;
-  if (co < Cout && ci < Cin)
-    v = w[((size_t)co * 9 + tap) * Cin + ci];
-  out[i] = v;
-}
-
 template <int MODE>
 void launch(const ConvArgs& a, hipStream_t st) {
   ConvArgs b = a;
   b.ntx = (a.W + 15) / 16;
   b.nchunk = (a.Cx + a.C2 + 15) / 16;
+  b.wp = static_cast<const float*>(a.wp) + f32_pack(a.Cout, a.Cx + a.C2).plain;
   // 8-row blocks (TN = 2) for small problems, and for POOL2 with TM = 4, whose 16-row variant
   // does not fit in 256 VGPRs
   const bool wide = a.Cout > 32;
@@ -219,12 +197,6 @@ void launch(const ConvArgs& a, hipStream_t st) {
 }  // namespace
 
 namespace aps {
-
-void pack_f32c16(const float* w, int Cout, int Cin, void* packed, hipStream_t st) {
-  const int n16 = (Cin + 15) / 16;  // fits the allocation, which counts 32-channel chunks
-  const size_t total = (size_t)((Cout + 16 * kMaxTM - 1) / (16 * kMaxTM)) * kMaxTM * 9 * n16 * 256;
-  k_pack_f32c16<<<(int)((total + 255) / 256), 256, 0, st>>>(w, Cout, Cin, n16, total, static_cast<float*>(packed));
-}
 
 void conv_f32(const ConvArgs& a, hipStream_t st) {
   if (a.mode == APS_CONV_POOL2) launch<APS_CONV_POOL2>(a, st);

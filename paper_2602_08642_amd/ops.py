@@ -259,7 +259,7 @@ class Net:
 def conv2d(x, layer_spec, packed, bias, mode: str = "direct", x2=None, out_dtype=None,
            ldy: int | None = None, out=None, train: bool = False):
     """One conv layer through aps_conv2d_fwd (mode: direct | pool2 | up2cat); train: through
-    aps_conv2d_fwd_train, packed by aps_conv_pack_weights_train."""
+    aps_conv2d_fwd_train."""
     _need(x, "x")
     N = x.shape[0]
     if mode == "direct":
