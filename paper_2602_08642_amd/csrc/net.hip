@@ -12,11 +12,11 @@ size_t esize(int dtype) { return dtype == APS_BF16 ? 2 : 4; }
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 int conv(const aps_conv_layer& L, const void* x, const void* x2, int N, int H, int W, int Cx,
-         int C2, int mode, int dtype, void* y, int ldy, int y_dtype, void* stream) {
+         int C2, int mode, int dtype, void* y, int ldy, int y_dtype, void* stream, bool train = false) {
   if (!L.w || !L.b) return APS_ERR_NULL;
   if (L.cin != Cx + C2) return APS_ERR_SHAPE;
-  return aps_conv2d_fwd(x, x2, N, H, W, Cx, C2, mode, L.w, L.b, L.cout, L.ksize, L.relu, dtype,
-                        y, ldy, y_dtype, stream);
+  return (train ? aps_conv2d_fwd_train : aps_conv2d_fwd)(x, x2, N, H, W, Cx, C2, mode, L.w, L.b, L.cout, L.ksize,
+                                                         L.relu, dtype, y, ldy, y_dtype, stream);
 }
 
 #define APS_TRY(expr)            \
@@ -201,11 +201,11 @@ int aps_density_predict_bwd(const aps_net* net, const void* const* packed_dgrad,
   void* nw = take(nws);
   void* wg = p;
   const size_t wg_bytes = ws_bytes - (size_t)(p - static_cast<char*>(ws));
-  // forward recomputation, layer by layer (the post-ReLU activations are the ReLU masks and
-  // the inputs of the weight gradients)
-  APS_TRY(conv(L[0], feat, nullptr, N, H, W, C, 0, APS_CONV_DIRECT, dt, a0, c0, dt, stream));
-  APS_TRY(conv(L[1], a0, nullptr, N, H, W, c0, 0, APS_CONV_DIRECT, dt, a1, c1, dt, stream));
-  APS_TRY(conv(L[2], a1, nullptr, N, H, W, c1, 0, APS_CONV_DIRECT, dt, z, 1, APS_F32, stream));
+  // forward recomputation, layer by layer, in the training pass (the post-ReLU activations are the
+  // ReLU masks and the inputs of the weight gradients)
+  APS_TRY(conv(L[0], feat, nullptr, N, H, W, C, 0, APS_CONV_DIRECT, dt, a0, c0, dt, stream, true));
+  APS_TRY(conv(L[1], a0, nullptr, N, H, W, c0, 0, APS_CONV_DIRECT, dt, a1, c1, dt, stream, true));
+  APS_TRY(conv(L[2], a1, nullptr, N, H, W, c1, 0, APS_CONV_DIRECT, dt, z, 1, APS_F32, stream, true));
   // budget normalisation: dLoss/dz
   APS_TRY(aps_normalize_density_bwd(z, N, H, W, budget_spp, uniform_frac, grad_s, gz, nw, nws,
                                     stream));
