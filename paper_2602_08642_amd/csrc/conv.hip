@@ -117,16 +117,6 @@ constexpr uint32_t kNoPixel = 0xffffffffu;
 // bf16 y > 0 (positive, finite or +inf), decided on the bits
 __device__ inline bool bf_pos(uint16_t b) { return (int16_t)b > 0 && (b & 0x7fffu) <= 0x7f80u; }
 
-// Orders this wave's LDS accesses across lanes: a compiler barrier for memory operations (the
-// LDS itself completes one wave's operations in program order).  Plain signal fences are not
-// enough where the two sides use different vector types, which type-based alias analysis may
-// then take as disjoint.
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Stores a wave's TN rows x 16 px x 16 TM channels: rounded to bf16, ReLU on the rounded bits
 // (round-to-nearest-even keeps the sign, so this equals rounding max(v, 0)).  A lane holds 4
 // channels of a pixel and its neighbours the same channels of other pixels, so stored as they are

@@ -51,6 +51,16 @@ __device__ inline TileId xcd_tile(int id, int ntiles, int nco) {
 }
 inline int xcd_grid(int ntiles, int nco) { return 8 * ((ntiles + 7) / 8) * nco; }
 
+// Orders this wave's LDS accesses across lanes: a compiler barrier for memory operations (the
+// LDS itself completes one wave's operations in program order).  Plain signal fences are not
+// enough where the two sides use different vector types, which type-based alias analysis may
+// then take as disjoint.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- 8-element vectors of the storage type ---------------------------------------------
 struct V8f {
   float v[8];

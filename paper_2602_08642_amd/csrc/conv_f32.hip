@@ -38,7 +38,7 @@
 // What bounds it: for 32-channel blocks one chunk's latency (load, scale, staging, MFMAs in turn, with
 // three blocks per CU) and 1000 vector instructions per wave and chunk beside 216 MFMAs; for 64-channel
 // blocks the MFMAs.  1920 x 1080, before (fp32 MFMA) and now:
-// 16 -> 32 162 -> 175 us, 32 -> 32 317 -> 191 us, 64 -> 64 (540 x 960) 322 -> 127 us, 128 -> 128
+// 16 -> 32 162 -> 156 us, 32 -> 32 317 -> 176 us, 64 -> 64 (540 x 960) 322 -> 127 us, 128 -> 128
 // (270 x 480) 298 -> 104 us, 384 -> 128 841 -> 292 us, 96 -> 32 899 -> 360 us; the U-Net 5.59 -> 2.36 ms.
 // Not kept: persistent blocks (fetching the next tile during the current one: registers spill),
 // weights of all three tap rows live at once (spills), 8 channels per staging load.
