@@ -33,6 +33,9 @@ constexpr int kPS = 48;     // elements per staged pixel: 96 bytes, so that the 
                             // bytes a 16-lane group reads fall on distinct banks
 constexpr int kCols = 32;   // columns per band = K of one MFMA
 constexpr long kWgBlocks = 512;  // two blocks of four waves per CU
+// Rounds of blocks whose partial sums the workspace holds; with more images than that a wave walks several
+// bands (384 -> 128 channels, 64 images of 256 x 256: 228 MB without, 4096 of 16 x 16: 1.8 GB).
+constexpr long kWgRounds = 4;
 
 struct Args {
   const uint16_t *x, *x2, *dy, *ym;
@@ -107,8 +110,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_sweep(Args a) {
       for (int s = 0; s < 2; ++s) acc[t][m][s] = f32x4{0.f, 0.f, 0.f, 0.f};
   bacc[0] = bacc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int unit = split * 4 + wave;
-  if (unit < a.nunit) {  // whole waves; the block meets again at the barriers below
+  // whole waves; the block meets again at the barriers below
+  for (int unit = split * 4 + wave; unit < a.nunit; unit += a.splits * 4) {
     const int n = unit / (a.nseg_c * a.nseg_r), u = unit % (a.nseg_c * a.nseg_r);
     const int x0 = (u % a.nseg_c) * kCols, y0 = (u / a.nseg_c) * a.R, y1 = min(y0 + a.R, H);
     const u16x8 zero = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
@@ -349,7 +352,9 @@ Plan plan(int N, int H, int W, int Cin, int Cout, int KS) {
   p.R = (int)R;
   p.nseg_r = (int)((H + R - 1) / R);
   p.nunit = N * p.nseg_c * p.nseg_r;
-  p.splits = (p.nunit + 3) / 4;
+  const long most = 4 * std::max(1L, kWgRounds * kWgBlocks / tiles);  // waves per channel tile
+  const long per = (p.nunit + most - 1) / most;  // bands per wave, as many for each as can be
+  p.splits = (int)((p.nunit + 4 * per - 1) / (4 * per));
   p.bytes = (size_t)p.splits * tiles * (KS * KS * 4 + 2) * 64 * sizeof(f32x4);
   return p;
 }
