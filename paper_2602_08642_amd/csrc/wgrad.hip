@@ -81,7 +81,8 @@ __device__ inline u16x8 row_load(const uint16_t* base, uint32_t bytes, uint32_t 
 }
 
 // VEC: dY (and mask) rows of whole aligned 16-byte pieces; else they are read element by element.
-template <int KS, int MODE, bool VEC>
+// MANY: more bands than waves (with the loop over bands, the others lose 1 to 2 %).
+template <int KS, int MODE, bool VEC, bool MANY>
 __global__ __launch_bounds__(256, 2) void k_wgrad_sweep(Args a) {
   constexpr int KK = KS * KS, R1 = KS / 2, XW = kCols + 2 * R1;
   constexpr int NF = KK * 4 + 2;                    // fragments of a wave's tile, bias included
@@ -260,6 +261,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_sweep(Args a) {
         }
       }
     }
+    if (!MANY) break;
   }
   // add the four waves' tiles, (0 + 2) + (1 + 3), and write the block's partial: fragment f of
   // the tile as 64 consecutive float4
@@ -395,9 +397,15 @@ void wgrad_sweep(const void* x, const void* x2, int mode, int N, int H, int W, i
   a.ntile = p.ncot * p.ncit;
   a.splits = p.splits;
   const int grid = (p.splits * a.ntile + 7) / 8 * 8;
+  const bool many = p.nunit > 4 * p.splits;
 #define APS_WG(KS, MODE)                                                   \
-  if (vec) k_wgrad_sweep<KS, MODE, true><<<grid, 256, 0, st>>>(a);         \
-  else k_wgrad_sweep<KS, MODE, false><<<grid, 256, 0, st>>>(a);
+  if (many) {                                                              \
+    if (vec) k_wgrad_sweep<KS, MODE, true, true><<<grid, 256, 0, st>>>(a); \
+    else k_wgrad_sweep<KS, MODE, false, true><<<grid, 256, 0, st>>>(a);    \
+  } else {                                                                 \
+    if (vec) k_wgrad_sweep<KS, MODE, true, false><<<grid, 256, 0, st>>>(a);\
+    else k_wgrad_sweep<KS, MODE, false, false><<<grid, 256, 0, st>>>(a);   \
+  }
 #define APS_WG_M(KS)                                                       \
   if (mode == APS_CONV_POOL2) { APS_WG(KS, APS_CONV_POOL2) }               \
   else if (mode == APS_CONV_UP2_CAT) { APS_WG(KS, APS_CONV_UP2_CAT) }      \
