@@ -119,35 +119,46 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_sweep(Args a) {
     // this lane's 16-byte pieces: X piece k = pixel (lane + 64 k) / 4, channels 8 (lane % 4) + [0,8)
     // of the input tile; dY piece k the same of the output tile
     const int g8 = 8 * (lane & 3), ci = cit * 32 + g8, co = cot * 32 + g8;
-    // byte offsets within a row; past its end where the piece is outside the image or the tensor
+    // byte offsets from the band's first column (a row's may not fit 32 bits); past the end where the
+    // piece is outside the image or the tensor
     constexpr uint32_t kOut = 0xfffffff0u;
+    const int xb = max(x0 - R1, 0), nx = min(x0 + kCols + R1, W) - xb, ny = min(kCols, W - x0);
+    const int ncx = (xb + nx + 1) / 2 - xb / 2;  // coarse columns (UP2_CAT)
     uint32_t xo[NX], so[NX], yo[2], mo[2];
 #pragma unroll
     for (int k = 0; k < NX; ++k) {
       const int p = (lane >> 2) + 16 * k, ix = x0 - R1 + p;
       const bool in = p < XW && ix >= 0 && ix < W && ci < Cin;
       if constexpr (MODE == APS_CONV_UP2_CAT) {
-        xo[k] = in && ci < a.Cx ? (uint32_t)((ix / 2) * a.Cx + ci) * 2 : kOut;
-        so[k] = in && ci >= a.Cx ? (uint32_t)(ix * a.C2 + ci - a.Cx) * 2 : kOut;
+        xo[k] = in && ci < a.Cx ? (uint32_t)((ix / 2 - xb / 2) * a.Cx + ci) * 2 : kOut;
+        so[k] = in && ci >= a.Cx ? (uint32_t)((ix - xb) * a.C2 + ci - a.Cx) * 2 : kOut;
       } else {
-        xo[k] = in ? (uint32_t)((MODE == APS_CONV_POOL2 ? 2 * ix : ix) * a.Cx + ci) * 2 : kOut;
+        xo[k] = in ? (uint32_t)((MODE == APS_CONV_POOL2 ? 2 : 1) * (ix - xb) * a.Cx + ci) * 2 : kOut;
       }
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int px = x0 + (lane >> 2) + 16 * k;
+      const int px = (lane >> 2) + 16 * k;
       // channels of [Cout, ldy) may come along: they only reach rows of dW that are not written
-      yo[k] = px < W && co < a.ldy ? (uint32_t)(px * a.ldy + co) * 2 : kOut;
-      mo[k] = px < W && co < a.Cout ? (uint32_t)(px * a.Cout + co) * 2 : kOut;
+      yo[k] = px < ny && co < a.ldy ? (uint32_t)(px * a.ldy + co) * 2 : kOut;
+      mo[k] = px < ny && co < a.Cout ? (uint32_t)(px * a.Cout + co) * 2 : kOut;
     }
+    // the band's first row of the image, and the elements from one of its rows to the next
+    const size_t img = (size_t)n * H * W;
+    const size_t xs = MODE == APS_CONV_POOL2 ? 4 * (size_t)W * a.Cx : MODE == APS_CONV_UP2_CAT ? (size_t)(W / 2) * a.Cx : (size_t)W * a.Cx;
+    const uint16_t* xp = MODE == APS_CONV_POOL2 ? a.x + (4 * img + 2 * xb) * a.Cx
+                         : MODE == APS_CONV_UP2_CAT ? a.x + (img / 4 + xb / 2) * a.Cx : a.x + (img + xb) * a.Cx;
+    const uint16_t* x2p = a.x2 + (img + xb) * a.C2;
+    const uint16_t* yp = a.dy + (img + x0) * a.ldy;
+    const uint16_t* mp = a.ym ? a.ym + (img + x0) * a.Cout : yp;
     u16x8 xr[NX], yr[2], mr[2];
     auto load_x = [&](int iy) {
       const bool in = iy >= 0 && iy < H;
       if constexpr (MODE == APS_CONV_POOL2) {
         // 2x2 mean in the order and rounding of the forward's input transform
-        const size_t rs = 2 * (size_t)W * a.Cx;
-        const uint16_t* q = a.x + ((size_t)n * H + (in ? iy : 0)) * 2 * rs;
-        const uint32_t nb = in ? (uint32_t)rs * 2 : 0u, dc = (uint32_t)a.Cx * 2;
+        const size_t rs = xs / 2;
+        const uint16_t* q = xp + (in ? iy : 0) * xs;
+        const uint32_t nb = in ? (uint32_t)(4 * nx) * a.Cx : 0u, dc = (uint32_t)a.Cx * 2;
 #pragma unroll
         for (int k = 0; k < NX; ++k) {
           // an offset past the end stays past it: kOut + dc does not wrap for the lanes in use
@@ -163,9 +174,9 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_sweep(Args a) {
         }
       } else if constexpr (MODE == APS_CONV_UP2_CAT) {
         const int r = in ? iy : 0;
-        const uint16_t* q = a.x + ((size_t)n * (H / 2) + r / 2) * (W / 2) * a.Cx;
-        const uint16_t* q2 = a.x2 + ((size_t)n * H + r) * W * a.C2;
-        const uint32_t nb = in ? (uint32_t)(W / 2) * a.Cx * 2 : 0u, nb2 = in ? (uint32_t)W * a.C2 * 2 : 0u;
+        const uint16_t* q = xp + (r / 2) * xs;
+        const uint16_t* q2 = x2p + r * ((size_t)W * a.C2);
+        const uint32_t nb = in ? (uint32_t)(2 * ncx) * a.Cx : 0u, nb2 = in ? (uint32_t)(2 * nx) * a.C2 : 0u;
         const bool has_x = cit * 32 < a.Cx, has_2 = cit * 32 + 32 > a.Cx;  // a tile may span both
 #pragma unroll
         for (int k = 0; k < NX; ++k) {
@@ -174,27 +185,27 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_sweep(Args a) {
           else xr[k] = row_load(q2, nb2, so[k]);
         }
       } else {
-        const uint16_t* q = a.x + ((size_t)n * H + (in ? iy : 0)) * W * a.Cx;
-        const uint32_t nb = in ? (uint32_t)W * a.Cx * 2 : 0u;
+        const uint16_t* q = xp + (in ? iy : 0) * xs;
+        const uint32_t nb = in ? (uint32_t)(2 * nx) * a.Cx : 0u;
 #pragma unroll
         for (int k = 0; k < NX; ++k) xr[k] = row_load(q, nb, xo[k]);
       }
     };
     auto load_y = [&](int py) {  // y0 <= py < y1 <= H
-      const uint16_t* q = a.dy + ((size_t)n * H + py) * W * a.ldy;
+      const uint16_t* q = yp + py * ((size_t)W * a.ldy);
       // without a mask an empty row (zeros): the load stays unconditional, so no wait is placed here
-      const uint16_t* m = a.ym ? a.ym + ((size_t)n * H + py) * W * a.Cout : q;
-      const uint32_t mb = a.ym ? (uint32_t)W * a.Cout * 2 : 0u;
+      const uint16_t* m = a.ym ? mp + py * ((size_t)W * a.Cout) : q;
+      const uint32_t mb = a.ym ? (uint32_t)(2 * ny) * a.Cout : 0u;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         if constexpr (VEC) {
-          yr[k] = row_load(q, (uint32_t)W * a.ldy * 2, yo[k]);
+          yr[k] = row_load(q, (uint32_t)(2 * ny) * a.ldy, yo[k]);
           mr[k] = row_load(m, mb, mo[k]);
         } else {
-          const int px = x0 + (lane >> 2) + 16 * k;
+          const int px = (lane >> 2) + 16 * k;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const bool ok = px < W && co + e < a.Cout;
+            const bool ok = px < ny && co + e < a.Cout;
             yr[k][e] = ok ? q[(size_t)px * a.ldy + co + e] : (uint16_t)0;
             if (a.ym) mr[k][e] = ok ? m[(size_t)px * a.Cout + co + e] : (uint16_t)0;
           }
