@@ -1406,8 +1406,10 @@ int aps_conv2d_bwd_data(const void* dy, const void* ymask, int ldy, int N, int H
   a.Cout = Cin;
   a.nchunk = (ldy + kChunk - 1) / kChunk;
   a.cvalid = Cout;
-  // the operator was packed for Cout input channels: the padded stride must give the same layout
-  if ((ldy + kChunk - 1) / kChunk != (Cout + kChunk - 1) / kChunk || conv_cg(ksize, ldy, Cin) != conv_cg(ksize, Cout, Cin))
+  // the operator was packed for Cout input channels: the padded stride must give the same layout (fp32
+  // 3x3: also that of the plain weights, in 16-channel chunks)
+  const int kc = dtype == APS_F32 && ksize == 3 && conv_cg(3, ldy, Cin) == 4 ? 16 : kChunk;
+  if ((ldy + kc - 1) / kc != (Cout + kc - 1) / kc || conv_cg(ksize, ldy, Cin) != conv_cg(ksize, Cout, Cin))
     return APS_ERR_SHAPE;
   if (dtype == APS_F32 && ksize == 3 && conv_cg(3, ldy, Cin) == 4 &&
       !fp32_offsets_fit(a.mode == kModeReluMask ? APS_CONV_DIRECT : a.mode, N, H, W, ldy, 0))
