@@ -713,8 +713,9 @@ __global__ void k_pack(const float* __restrict__ w, int Cout, int KS, int Cin, i
   else out[i] = v;
 }
 
-// fp32 3x3 convolutions in 32-channel chunks run only in k_conv_split (conv_f32.hip), which
-// addresses its inputs with 32-bit element offsets
+// fp32 3x3 convolutions in 32-channel chunks: inputs of 2^31 elements and more are refused.  k_conv_f32 (the
+// training forward) addresses an input with 32-bit element offsets; k_conv_split would take them, but the
+// passes of a layer accept the same sizes.
 bool fp32_offsets_fit(int mode, int N, int H, int W, int Cx, int C2) {
   const size_t px = (size_t)N * H * W;
   const size_t ex = mode == APS_CONV_POOL2 ? 4 * px * Cx : mode == APS_CONV_UP2_CAT ? px / 4 * Cx : px * Cx;
@@ -896,15 +897,15 @@ void dispatch_tiles(const ConvArgs& a, hipStream_t st) {
   }
   if constexpr (sizeof(T) == 4 && KS == 3 && CG == 4) {
     conv_split(a, st);  // sizes checked by the entry points (fp32_offsets_fit)
-    return;
-  }
-  const bool big = (size_t)a.H * a.W >= 64 * 64;
-  if (a.Cout <= 16) {
-    if (big) launch_conv<T, TO, KS, 1, 4, CG>(a, st); else launch_conv<T, TO, KS, 1, 2, CG>(a, st);
-  } else if (a.Cout <= 32) {
-    if (big) launch_conv<T, TO, KS, 2, 4, CG>(a, st); else launch_conv<T, TO, KS, 2, 2, CG>(a, st);
   } else {
-    if (big) launch_conv<T, TO, KS, 4, 4, CG>(a, st); else launch_conv<T, TO, KS, 4, 2, CG>(a, st);
+    const bool big = (size_t)a.H * a.W >= 64 * 64;
+    if (a.Cout <= 16) {
+      if (big) launch_conv<T, TO, KS, 1, 4, CG>(a, st); else launch_conv<T, TO, KS, 1, 2, CG>(a, st);
+    } else if (a.Cout <= 32) {
+      if (big) launch_conv<T, TO, KS, 2, 4, CG>(a, st); else launch_conv<T, TO, KS, 2, 2, CG>(a, st);
+    } else {
+      if (big) launch_conv<T, TO, KS, 4, 4, CG>(a, st); else launch_conv<T, TO, KS, 4, 2, CG>(a, st);
+    }
   }
 }
 
@@ -1059,28 +1060,26 @@ struct WgradArgs {
   float* part;          // [splits][CoutP][KS*KS][CinP]
 };
 
-template <typename T>
-__device__ inline void frag_load_lds(Frag<T>& f, const T* p);
-template <>
-__device__ inline void frag_load_lds<float>(Frag<float>& f, const float* p) {
+// as frag_load, from LDS rows without 16-byte alignment
+__device__ inline void frag_load_lds(Frag<float>& f, const float* p) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) f.v[e] = p[e];
 }
-template <typename T, int KS>
+template <int KS>
 __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
   constexpr int R = KS / 2;
   constexpr int NP = kWgRows * kWgCols;
   constexpr int XW = kWgCols + 2 * R, XH = kWgRows + 2 * R;
   constexpr int YS = NP + 8;        // per-cout row of dY (elements)
   constexpr int XS = XH * XW + 8;   // per-cin plane of X (elements)
-  __shared__ __attribute__((aligned(16))) T dYs[32 * YS];
-  __shared__ __attribute__((aligned(16))) T Xs[32 * XS];
+  __shared__ __attribute__((aligned(16))) float dYs[32 * YS];
+  __shared__ __attribute__((aligned(16))) float Xs[32 * XS];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int split = blockIdx.x, cot = blockIdx.y, c = blockIdx.z;
   const int m = wave & 1, j = wave >> 1;
   const int H = a.in.H, W = a.in.W;
-  const T* dy = static_cast<const T*>(a.dy);
-  const T* ym = static_cast<const T*>(a.ymask);
+  const float* dy = static_cast<const float*>(a.dy);
+  const float* ym = static_cast<const float*>(a.ymask);
 
   f32x4 acc[KS * KS];
 #pragma unroll
@@ -1102,20 +1101,20 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           if (co + e < a.Cout) {
-            float g_ = Ld<T>::get(dy, pix * a.ldy + co + e);
-            if (ym && !(Ld<T>::get(ym, pix * a.Cout + co + e) > 0.f)) g_ = 0.f;
+            float g_ = dy[pix * a.ldy + co + e];
+            if (ym && !(ym[pix * a.Cout + co + e] > 0.f)) g_ = 0.f;
             v[e] = g_;
           }
         }
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dYs[(g * 8 + e) * YS + p] = f2t<T>(v[e]);
+      for (int e = 0; e < 8; ++e) dYs[(g * 8 + e) * YS + p] = v[e];
     }
     for (int it = tid; it < XH * XW * 4; it += 256) {
       const int g = it & 3, p = it >> 2;
       const int r = p / XW, col = p % XW;
-      T tmp[8];
-      stage8<T>(a.in, n, y0 - R + r, x0 - R + col, c * kChunk + g * 8, tmp);
+      float tmp[8];
+      stage8<float>(a.in, n, y0 - R + r, x0 - R + col, c * kChunk + g * 8, tmp);
 #pragma unroll
       for (int e = 0; e < 8; ++e) Xs[(g * 8 + e) * XS + p] = tmp[e];
     }
@@ -1124,12 +1123,12 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
     for (int r = 0; r < kWgRows; ++r) {
 #pragma unroll
       for (int s = 0; s < kWgCols / 32; ++s) {
-        Frag<T> af;
+        Frag<float> af;
         frag_load_lds(af, dYs + (m * 16 + (lane & 15)) * YS + r * kWgCols + 32 * s + 8 * (lane >> 4));
 #pragma unroll
         for (int tap = 0; tap < KS * KS; ++tap) {
           const int dyy = tap / KS - R, dxx = tap % KS - R;
-          Frag<T> bf;
+          Frag<float> bf;
           frag_load_lds(bf, Xs + (j * 16 + (lane & 15)) * XS + (r + R + dyy) * XW +
                                 (32 * s + 8 * (lane >> 4) + R + dxx));
           acc[tap] = mma(af, bf, acc[tap]);
@@ -1189,9 +1188,8 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
 // p0 + r, p0 + r + R, ... in order into four accumulators (independent loads in flight), then the
 // lanes of a channel are added in lane order.  The second pass sums the block partials of one
 // channel per block: a fixed stride per thread, then a fixed pairwise tree.
-template <typename T>
-__global__ __launch_bounds__(256) void k_bias_partial(const T* __restrict__ dy,
-                                                      const T* __restrict__ ym, int ldy, int Cout,
+__global__ __launch_bounds__(256) void k_bias_partial(const float* __restrict__ dy,
+                                                      const float* __restrict__ ym, int ldy, int Cout,
                                                       size_t npix, size_t per,
                                                       float* __restrict__ part) {
   __shared__ float red[256];
@@ -1199,8 +1197,8 @@ __global__ __launch_bounds__(256) void k_bias_partial(const T* __restrict__ dy,
   const int R = 256 / Cout;  // Cout <= 256
   const int co = t % Cout, r = t / Cout;
   auto g = [&](size_t p) {
-    const float v = Ld<T>::get(dy, p * ldy + co);
-    return ym && !(Ld<T>::get(ym, p * Cout + co) > 0.f) ? 0.f : v;
+    const float v = dy[p * ldy + co];
+    return ym && !(ym[p * Cout + co] > 0.f) ? 0.f : v;
   };
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   if (r < R) {
@@ -1505,15 +1503,15 @@ int aps_conv2d_bwd_weight(const void* x, const void* x2, int mode, int N, int H,
   float* bpart = reinterpret_cast<float*>(static_cast<char*>(ws) + ((p.part_bytes + 255) / 256) * 256);
   hipStream_t st = as_stream(stream);
   dim3 grid(p.splits, p.CoutP / 32, p.nchunk);
-  if (ksize == 3) k_wgrad<float, 3><<<grid, 256, 0, st>>>(a);
-  else k_wgrad<float, 1><<<grid, 256, 0, st>>>(a);
+  if (ksize == 3) k_wgrad<3><<<grid, 256, 0, st>>>(a);
+  else k_wgrad<1><<<grid, 256, 0, st>>>(a);
   const size_t nw = (size_t)Cout * ksize * ksize * Cin;
   k_wgrad_reduce<<<(unsigned)((nw + 31) / 32), 256, 0, st>>>(a.part, p.splits, Cout,
                                                                 ksize * ksize, Cin, p.CoutP, p.CinP,
                                                                 dw);
   if (db) {
     const size_t npix = (size_t)N * H * W;
-    k_bias_partial<float><<<(unsigned)p.bias_blocks, 256, 0, st>>>(
+    k_bias_partial<<<(unsigned)p.bias_blocks, 256, 0, st>>>(
         static_cast<const float*>(dy), static_cast<const float*>(ymask), ldy, Cout, npix, p.bias_per,
         bpart);
     k_bias_reduce<<<Cout, 256, 0, st>>>(bpart, (int)p.bias_blocks, Cout, db);

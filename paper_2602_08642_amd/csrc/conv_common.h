@@ -159,9 +159,6 @@ __device__ inline void store_out<uint16_t>(uint16_t* p, int ldy, int co0, int Co
   }
 }
 
-// Epilogue shared by the convolution kernels: bias, optional ReLU, store; with HEAD, the fused
-// 1x1 head.  acc[m][j] holds output rows row0 + j, channels 16 (cob TM + m) + 4 (lane / 16) + q,
-// pixel column tx0 + lane % 16.  Xs is the block's LDS tile, reused by the head's re-layout.
 // s_waitcnt immediate (gfx9 encoding) that waits for all vector memory operations only:
 // vmcnt = 0, expcnt = 7 and lgkmcnt = 15 (no wait on those).
 constexpr int kWaitVm0 = 0x0F70;
@@ -175,6 +172,9 @@ constexpr int head_lds_elems() {
   return 4 * 16 * (TM * 16 + (sizeof(T) == 2 ? 8 : 4)) + 4 * 16 * 16 * HM * (int)(sizeof(TO) / sizeof(T));
 }
 
+// Epilogue shared by the convolution kernels: bias, optional ReLU, store; with HEAD, the fused
+// 1x1 head.  acc[m][j] holds output rows row0 + j, channels 16 (cob TM + m) + 4 (lane / 16) + q,
+// pixel column tx0 + lane % 16.  Xs is the block's LDS tile, reused by the head's re-layout.
 template <typename T, typename TO, int TM, int TN, int HEAD, bool BIAS_IN_ACC = false>
 __device__ inline void conv_epilogue(const ConvArgs& a, f32x4 (&acc)[TM][TN], int row0, int tx0,
                                      int cob, int n, int lane, int wave, T* Xs) {
