@@ -117,6 +117,21 @@ __device__ inline f32x4 conv_input4(const ConvArgs& a, int n, int iy, int ix, in
   return v;
 }
 
+// A wave's values reduced, in lane 63 (rows of 16 lanes by shifts, then across the rows)
+template <int CTRL, typename F>
+__device__ inline uint32_t dpp_step(uint32_t v, F f) {
+  return f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false));
+}
+template <typename F>
+__device__ inline uint32_t wave_reduce(uint32_t v, F f) {
+  v = dpp_step<0x111>(v, f);  // row_shr:1, 2, 4, 8
+  v = dpp_step<0x112>(v, f);
+  v = dpp_step<0x114>(v, f);
+  v = dpp_step<0x118>(v, f);
+  v = dpp_step<0x142>(v, f);  // row_bcast:15
+  return dpp_step<0x143>(v, f);  // row_bcast:31
+}
+
 // Fragment f (in units of 512 halves) of channel tile ct, tap t, chunk c, half p (0: h, 1: l)
 __device__ inline uint32_t wfrag(int ct, int t, int c, int p, int nchunk) {
   return (uint32_t)(((ct * 9 + t) * nchunk + c) * 2 + p) * 512u;
@@ -178,7 +193,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
   constexpr int PL = NPX * 32;          // halves per plane
   constexpr int XS_HEAD = HEAD ? 2 * head_lds_elems<float, float, TM, HEAD>() : 0;
   __shared__ __attribute__((aligned(16))) uint16_t Xs[2 * PL > XS_HEAD ? 2 * PL : XS_HEAD];
-  __shared__ float red[2][4];
+  __shared__ uint32_t red[2][4];
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const TileId tid_ = xcd_tile(blockIdx.x, a.ntiles, a.nco);
@@ -325,21 +340,18 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
         mx = fmaxf(mx, __builtin_fabsf(v));
         mw = std::min(mw, (__builtin_bit_cast(uint32_t, v) << 1) - 1);
       }
-    float mn = mw == ~0u ? __builtin_inff() : __builtin_bit_cast(float, (mw + 1) >> 1);
-    mx = wave_max(mx);
-    mn = wave_max(-mn);
-    if (lane == 0) {
-      red[0][wave] = mx;
-      red[1][wave] = mn;
+    const uint32_t mb = wave_reduce(__builtin_bit_cast(uint32_t, mx), [](uint32_t x, uint32_t y) { return std::max(x, y); });
+    mw = wave_reduce(mw, [](uint32_t x, uint32_t y) { return std::min(x, y); });
+    if (lane == 63) {
+      red[0][wave] = mb;
+      red[1][wave] = mw;
     }
     __syncthreads();
-    auto most = [&](int i) { return fmaxf(fmaxf(red[i][0], red[i][1]), fmaxf(red[i][2], red[i][3])); };
-    auto uniform = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
-    mx = uniform(most(0));
-    mn = -uniform(most(1));
+    const uint32_t most = __builtin_amdgcn_readfirstlane(std::max(std::max(red[0][0], red[0][1]), std::max(red[0][2], red[0][3])));
+    const uint32_t least = __builtin_amdgcn_readfirstlane(std::min(std::min(red[1][0], red[1][1]), std::min(red[1][2], red[1][3])));
     bool part = false;  // elements remain for another pass over the chunk
-    if (mx > 0.f) {
-      const int fh = exp_field(mx), fl = exp_field(mn);
+    if (most) {
+      const int fh = std::max((int)(most >> 23), 1), fl = std::max((int)((least + 1) >> 24), 1);  // exponent fields
       if (exhi < exlo || fh + ex > kTop || fl + ex < kLow) {
         // in the middle of what holds them all, so that few chunks move it; else for the largest
         const int hi = kTop - fh, lo = kLow - fl, en = std::min(lo <= hi ? (lo + hi) >> 1 : hi, 126), d = en - ex;
