@@ -111,8 +111,8 @@ int aps_conv2d_fwd(const void* x, const void* x2, int N, int H, int W, int Cx, i
                    int dtype, void* y, int ldy, int y_dtype, void* stream);
 
 /* The forward pass of a training layer with a ReLU, whose signs the backward pass uses: fp32 3x3
- * layers in plain fp32 products (order: bias, 16-channel chunks, dx outer, dy inner); otherwise
- * aps_conv2d_fwd.  aps_conv_pack_weights and aps_conv_pack_weights_train pack the same, for both. */
+ * layers in plain fp32 products (order: bias, 16-channel chunks, dx outer, dy inner), whose bits are
+ * not those of aps_conv2d_fwd; otherwise aps_conv2d_fwd.  aps_conv_pack_weights and aps_conv_pack_weights_train pack the same, for both. */
 int aps_conv_pack_weights_train(const float* w, int Cout, int ksize, int Cin, int dtype, void* packed,
                                 void* stream);
 int aps_conv2d_fwd_train(const void* x, const void* x2, int N, int H, int W, int Cx, int C2, int mode,

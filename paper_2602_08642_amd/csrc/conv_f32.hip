@@ -23,8 +23,9 @@
 // half of the elements at 2^-30 or 2^-60 of the others, two passes, 290 and 182; plain products in every
 // block 450 and 340.  (A scale for the typical element, with the outputs that meet a larger one summed
 // again one by one, took 37 and 36 ms for half of the elements 2^30 apart.)
-// Error against FP64 (normwise; fp32 MFMA kernels in brackets): 128 -> 128 channels 3.7e-7 (4.3e-7),
-// the U-Net's heads at 1920 x 1080 at most 1.6e-6 (1.7e-6).
+// What the halves leave out: the last of 24 bits where l rounds, and l_x l_w, up to 2^-22 of a product.
+// Error against FP64 (normwise; fp32 MFMA kernels in brackets): 128 -> 128 channels 2.4e-7 (4.2e-7),
+// the U-Net's heads at 1920 x 1080 7.9e-7 (1.5e-6).
 //
 // Tiling as k_conv_lds: blocks of 4 waves stacked vertically, TN rows x 16 px each, all sharing TM
 // m-tiles; the chunk's input tile with its halo in LDS as two planes (64-byte pixels, 16-byte
@@ -35,11 +36,11 @@
 // One order of sums for every entry point and size: 32-channel chunks, taps dx outer and dy inner, then
 // the bias.  Powers of two change no bits, so the tile an output lies in matters only where it takes
 // several passes over a chunk or plain products.
-// What bounds it: for 32-channel blocks one chunk's latency (load, scale, staging, MFMAs in turn, with
+// What bounds it: for 32-channel blocks one chunk's latency (load, range, staging, MFMAs in turn, with
 // three blocks per CU) and 1000 vector instructions per wave and chunk beside 216 MFMAs; for 64-channel
 // blocks the MFMAs.  1920 x 1080, before (fp32 MFMA) and now:
-// 16 -> 32 162 -> 156 us, 32 -> 32 317 -> 176 us, 64 -> 64 (540 x 960) 322 -> 127 us, 128 -> 128
-// (270 x 480) 298 -> 104 us, 384 -> 128 841 -> 292 us, 96 -> 32 899 -> 360 us; the U-Net 5.59 -> 2.36 ms.
+// 16 -> 32 162 -> 156 us, 32 -> 32 317 -> 176 us, 64 -> 64 (960 x 540) 322 -> 125 us, 128 -> 128
+// (480 x 270) 298 -> 105 us, 384 -> 128 841 -> 303 us, 96 -> 32 899 -> 363 us; the U-Net 5.59 -> 2.37 ms.
 // Not kept: persistent blocks (fetching the next tile during the current one: registers spill),
 // weights of all three tap rows live at once (spills), 8 channels per staging load.
 #include <algorithm>
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
   const int Cin = a.Cx + a.C2;
   // This thread stages channels [g4, g4 + 4) of tile pixels tid / 8 + 32 k: a wave's load reads 8
   // pixels' whole 128-byte chunks (with 8 channels per thread and 16 pixels per load the same bytes
-  // cost the address unit twice the cycles, which bounded the 32-channel layers).
+  // cost the address unit twice the cycles).
   const int g4 = (tid & 7) * 4, pl = tid >> 3;
   // Byte offsets at chunk 0 from the tile's first input row; past the end (reads as zeros) where
   // the pixel is outside the image.

@@ -13,8 +13,8 @@
 // channel block only.  The four waves of a block (four bands) add their tiles in LDS in a fixed
 // order and write one partial per block; k_wgrad_sweep_reduce adds the partials in a fixed order.
 // What bounds it: a step is about 450 instructions for 36 MFMAs, and its operand reads wait on the
-// LDS between them (MFMA busy 20 % of a wave's life, LDS 22 %), so two waves per SIMD run as fast
-// as one each: the launches of the two-block rule below.  For one channel tile the reads of X, dY
+// LDS between them (over the concat layers of a training step MFMA busy 17 %, LDS 21 %), so two waves
+// per SIMD run as fast as one each: the launches of the two-block rule below.  For one channel tile the reads of X, dY
 // and the mask (52 MB at 32 -> 32, 4 x 256 x 256) set 10 us of it.  The element-wise staging into
 // channel-major LDS rows that this replaces took, with its separate bias and split reductions,
 // 95 us at 32 -> 32 and 4 x 256 x 256 (64 + 7 + 10 + 4 us, gaps included); the two kernels here
