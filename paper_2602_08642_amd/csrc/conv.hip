@@ -734,12 +734,13 @@ int conv_cg(int KS, int Cin, int Cout) {
   return g <= 1 ? 1 : (g <= 2 ? 2 : 4);
 }
 
+// elements of the layout of k_pack
 size_t packed_elems(int Cout, int KS, int Cin) {
   const size_t nct = (size_t)((Cout + 16 * kMaxTM - 1) / (16 * kMaxTM)) * kMaxTM;
   const int cg = conv_cg(KS, Cin, Cout);
   if (cg < 4) return nct * ((KS * KS * cg + 3) / 4) * 512;
-  const size_t nchunk = (size_t)(Cin + kChunk - 1) / kChunk, elems = nct * KS * KS * nchunk * 512;
-  return KS == 3 ? std::max(elems, f32_pack(Cout, Cin).total) : elems;
+  const size_t nchunk = (size_t)(Cin + kChunk - 1) / kChunk;
+  return nct * KS * KS * nchunk * 512;
 }
 
 template <typename T, typename TO, int KS, int TM, int TN, int CG>
@@ -1270,7 +1271,8 @@ extern "C" {
 
 size_t aps_conv_packed_elems(int Cout, int ksize, int Cin) {
   if (Cout <= 0 || Cin <= 0 || (ksize != 1 && ksize != 3)) return 0;
-  return packed_elems(Cout, ksize, Cin);
+  const size_t n = packed_elems(Cout, ksize, Cin);
+  return ksize == 3 && conv_cg(3, Cin, Cout) == 4 ? std::max(n, f32_pack(Cout, Cin).total) : n;  // k_pack_split's
 }
 
 static int pack_impl(const float* w, int Cout, int ksize, int Cin, int dtype, void* packed,
