@@ -6,8 +6,8 @@
 // its 24 bits, and x w = h_x h_w + h_x l_w + l_x h_w up to 2^-22 of the product: three
 // v_mfma_f32_16x16x32_f16 with fp32 accumulation do the work of eight v_mfma_f32_16x16x4_f32, and
 // the sum has a fifth of the roundings.  Range: the operands are scaled by powers of two, which is
-// exact, and both l halves carry a factor 2^11, which keeps their bits above the fp16 subnormals: all of
-// an operand's bits are there down to 2^-26 of the largest (kTop, kLow).  The cross products, 2^11 too
+// exact, and both l halves carry a factor 2^11, which keeps their last places on fp16's grid (2^-24): an
+// operand's bits are there down to 2^-26 of the largest (kTop, kLow).  The cross products, 2^11 too
 // large, are summed apart and added once per chunk.
 //  * Weights per output channel at packing time, the largest to [2^14, 2^15); the exponents are in a
 //    table behind the weights.  A channel whose weights are further apart than 2^26, or not finite, puts
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 3) void k_conv_split(ConvArgs a)
       for (int e = 0; e < 4; e += 2) {
         const float v0 = px[k][e], v1 = px[k][e + 1];
         const f16x2 h2 = __builtin_convertvector(f32x2{v0 * sx, v1 * sx}, f16x2);
-        // v sx - h is exact; times 2^11 it has the range of h, not the subnormals below it
+        // v sx - h is exact; times 2^11 its last place is on fp16's grid
         const f16x2 l2 = __builtin_convertvector(f32x2{__builtin_fmaf(v0, sx, -(float)h2[0]) * 2048.f,
                                                        __builtin_fmaf(v1, sx, -(float)h2[1]) * 2048.f}, f16x2);
         hv[e] = h2[0];
